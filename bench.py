@@ -165,16 +165,18 @@ def krylov_roofline(ctx, s, st, t_launch_ms, launches_per_pass=1):
     and index read once per Krylov step and shared by the atom's four columns,
     plus the pattern outputs 2 n_pat 8 B and the spectra 2 nu 8 B) over the
     launch's duration, against HBM peak; the streamed blocks actually issued
-    per launch (every step re-reads each non-cached block, 256 B, per column)
-    against the vector-memory ceiling; FP64 rate."""
+    per launch (for each pair of an atom's columns, every step re-reads the H
+    half, 128 B, of each non-cached block, and the projection the S half of
+    every block once per four basis vectors of each) against the vector-memory
+    ceiling; FP64 rate."""
     nu = s.nu
     M = 4 * s.n_atoms
     bytes_pass = 20.0 * nu * st["sum_cluster_nnz"] + 16.0 * ctx.nnz + 16.0 * nu * M
     per_launch = bytes_pass / max(launches_per_pass, 1)
     achieved = per_launch / (t_launch_ms * 1e-3) / 1e9
-    streamed_blocks = max(0.0, st["sum_cluster_nnz"] / 16.0
-                          - s.n_atoms * float(st["krylov_cache_blocks"]))
-    vmem = 4.0 * nu * streamed_blocks * 256.0 / max(launches_per_pass, 1)
+    blocks = st["sum_cluster_nnz"] / 16.0
+    streamed_blocks = max(0.0, blocks - s.n_atoms * float(st["krylov_cache_blocks"]))
+    vmem = 2.0 * 128.0 * (nu * streamed_blocks + -(-nu // 4) * blocks) / max(launches_per_pass, 1)
     vmem_gbs = vmem / (t_launch_ms * 1e-3) / 1e9
     return {
         "bound": "hbm",

@@ -35,10 +35,9 @@
  *     coefficient of H_{r c} in E_band = sum_r sum_c H_{r c} rho_{c r}.
  *   - Environment, read when a context first needs the value:
  *     MAG_SCRATCH_GB (default 8) bounds the per-column scratch of one chunk
- *     of columns; MAG_AUTOTUNE=0 keeps every Krylov launch plan at its
- *     default instead of timing the candidates; MAG_LDS_CACHE=0 makes new
- *     plans stream every matrix block instead of caching a cluster's first
- *     blocks in LDS.  At nu <= 30 the last two change no result bit.
+ *     of columns; MAG_LDS_CACHE=0 makes new plans stream every matrix block
+ *     instead of caching a cluster's first blocks in LDS, which changes no
+ *     result bit.
  */
 #ifndef MAG_H
 #define MAG_H
@@ -86,8 +85,8 @@ enum mag_workflow {
 };
 
 /* Launch schedule of the per-column Krylov kernels.  Columns are grouped into
- * buckets by cluster size; each bucket runs in the workgroup shape and
- * occupancy that the library timed fastest on first use.  PERSISTENT: per
+ * buckets by cluster size; each bucket runs in a workgroup shape of its own,
+ * which follows from nu and the cluster size.  PERSISTENT: per
  * bucket, one launch of resident workgroups pulling columns from eight
  * device queues of spatially contiguous columns (one per XCD, with
  * stealing).  GRID: per bucket, one launch with one workgroup per column.
@@ -486,23 +485,23 @@ typedef struct {
   int32_t workflow_used;   /* mag_workflow of the last solve (never AUTO) */
   int32_t krylov_buckets;  /* cluster-size buckets (workgroup shapes) of the last pass 1 */
   int32_t krylov_tpb;      /* threads per workgroup of the largest bucket's plan */
-  double autotune_ms;      /* time spent timing launch plans (first use of a shape) */
+  double autotune_ms;      /* time spent timing launch plans (0: they follow from the sizes) */
   double t_icohp_ms;       /* last mag_icohp (after pass 2) */
   double t_cohp_ms;        /* last mag_cohp */
   double t_md_step_ms;     /* last mag_md_run: average wall time of one step */
   double t_cocg_ms;        /* last mag_cocg_columns (its kernels) */
   double t_forces_exact_ms; /* last mag_forces_exact */
-  int32_t krylov_cache_blocks; /* H/S blocks of each cluster held in LDS by the largest bucket's plan */
+  int32_t krylov_cache_blocks; /* H blocks of each cluster held in LDS by the largest bucket's plan */
   /* the launch plan of each cluster-size bucket of the last pass 1 (bucket b
      holds the clusters between the row capacities of the shapes b-1 and b;
      entries of unused buckets are 0) */
   int32_t plan_threads[MAG_STATS_BUCKETS];    /* threads per workgroup */
-  int32_t plan_rows[MAG_STATS_BUCKETS];       /* cluster rows per thread */
+  int32_t plan_rows[MAG_STATS_BUCKETS];       /* cluster rows of a thread's basis vectors */
   int32_t plan_per_cu[MAG_STATS_BUCKETS];     /* persistent workgroups per CU */
-  int32_t plan_cache[MAG_STATS_BUCKETS];      /* cluster blocks cached in LDS */
-  int32_t plan_candidates[MAG_STATS_BUCKETS]; /* plans timed for the bucket (0: not tuned) */
+  int32_t plan_cache[MAG_STATS_BUCKETS];      /* H blocks of a cluster cached in LDS at most */
+  int32_t plan_candidates[MAG_STATS_BUCKETS]; /* plans the bucket had to choose from (1) */
   int64_t plan_columns[MAG_STATS_BUCKETS];    /* columns of the bucket */
-  double plan_us_per_col[MAG_STATS_BUCKETS];  /* the chosen plan's timed us per column */
+  double plan_us_per_col[MAG_STATS_BUCKETS];  /* 0: plans are not timed */
 } mag_stats;
 
 int mag_get_stats(mag_ctx* ctx, mag_stats* out);

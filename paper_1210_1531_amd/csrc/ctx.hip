@@ -349,7 +349,7 @@ struct GraphLists {
   std::vector<int64_t> slot_base;          // host: per chunk, offset into slots
 };
 
-// ---- Krylov launch plans and their tuning
+// ---- Krylov launch plans
 
 static size_t lds_per_cu(int device) {
   int v = 0;
@@ -362,114 +362,25 @@ static size_t lds_per_cu(int device) {
   return (size_t)v;
 }
 
-// largest block cache for `per_cu` workgroups of a shape on one CU (0 if the
-// cache is switched off or does not fit)
-static size_t cache_bytes(int shape, int per_cu, int device) {
-  const char* env = std::getenv("MAG_LDS_CACHE");
-  if (env && std::atoi(env) == 0) return 0;
-  const size_t slot = (size_t)CSLOT_BYTES;
-  const long share = (long)(lds_per_cu(device) / per_cu) - (long)krylov_static_lds(shape) - 512;
-  if (share < (long)slot) return 0;
-  size_t dyn = ((size_t)share / slot) * slot;
-  dyn = std::min(dyn, (size_t)krylov_cache_blocks((size_t)1 << 30) * slot);
-  while (dyn > 0 && krylov_occupancy(shape, dyn) < per_cu) dyn -= slot;
-  return dyn;
-}
-
-static KrylovPlan make_plan(int shape, int per_cu, int device) {
-  KrylovPlan p;
-  p.shape = shape;
-  p.per_cu = per_cu;
-  p.dyn = cache_bytes(shape, per_cu, device);
-  p.cache = krylov_cache_blocks(p.dyn);
-  return p;
-}
-
-// the plan of bucket b (default: its own shape, as many workgroups per CU as
-// fit, the LDS left over as block cache)
-KrylovPlan& krylov_plan(mag_ctx* ctx, const std::vector<KrylovShapeInfo>& shapes, int b, int ncu) {
-  (void)ncu;
-  const auto key = std::make_pair(shapes[b].cap, shapes[b].id);
+// the plan of bucket b: its shape, as many workgroups per CU as its registers
+// and least LDS allow, and the rest of the LDS to the block cache.  The shape
+// follows from nu and the cluster size, so there is nothing to time.
+KrylovPlan& krylov_plan(mag_ctx* ctx, const std::vector<KrylovShapeInfo>& shapes, int b) {
+  const int id = shapes[b].id;
+  const auto key = std::make_pair(shapes[b].cap, id);
   auto it = ctx->kplans.find(key);
   if (it != ctx->kplans.end()) return it->second;
-  const int occ = std::max(1, krylov_occupancy(shapes[b].id, 0));
-  KrylovPlan p = make_plan(shapes[b].id, occ, ctx->device);
-  const char* env = std::getenv("MAG_AUTOTUNE");
-  p.tuned = env && std::atoi(env) == 0;  // tuning off: keep the default
+  KrylovPlan p;
+  p.shape = id;
+  p.per_cu = std::max(1, krylov_occupancy(id, krylov_pool_min(id)));
+  const long share =
+      (long)(lds_per_cu(ctx->device) / p.per_cu) - (long)krylov_static_lds(id) - 512;
+  p.dyn = std::max((size_t)std::max(share, 0L) / 1024 * 1024, krylov_pool_min(id));
+  while (p.dyn > krylov_pool_min(id) && krylov_occupancy(id, p.dyn) < p.per_cu)
+    p.dyn = std::max(p.dyn - 1024, krylov_pool_min(id));
+  const char* env = std::getenv("MAG_LDS_CACHE");
+  p.cache = (env && std::atoi(env) == 0) ? 0 : krylov_cache_blocks(id, p.dyn);
   return ctx->kplans.emplace(key, p).first->second;
-}
-
-// Time the candidate plans of bucket b -- its own shape and every larger one,
-// each with 1 .. (occupancy) workgroups per CU and the largest block cache
-// that leaves them -- on a sample of the bucket's columns, and keep the
-// fastest.  Every candidate computes the same columns (the results do not
-// depend on the plan), so the sample's outputs are simply overwritten by the
-// real launch.
-int krylov_tune(mag_ctx* ctx, const std::vector<KrylovShapeInfo>& shapes, int b,
-                const KrylovArgs& ka, int64_t off, int64_t nb, int ncu,
-                const int32_t* hslots, const int32_t* hcols) {
-  KrylovPlan& plan = krylov_plan(ctx, shapes, b, ncu);
-  if (plan.tuned) return MAG_OK;
-  plan.tuned = true;
-  if (nb < ncu) return MAG_OK;  // too few columns to fill the device: keep the default
-  const int64_t S = std::min<int64_t>(nb, 4 * (int64_t)ncu);
-  // queue ranges over the sample, in the spare queue slot after the buckets
-  std::vector<int32_t> scols(S);
-  for (int64_t i = 0; i < S; ++i) scols[i] = hcols[hslots[i]];
-  const std::vector<int64_t> qb = queue_ranges(ctx, scols.data(), S);
-  int64_t* dq = ctx->k_qbeg.as<int64_t>() + (KRYLOV_QUEUES + 1) * (int64_t)shapes.size();
-  HIPCHK(hipMemcpyAsync(dq, qb.data(), sizeof(int64_t) * qb.size(), hipMemcpyHostToDevice,
-                        ctx->stream));
-  TRY(sync(ctx));
-  int32_t* dc = ctx->k_queue.as<int32_t>() + KRYLOV_QUEUES * (int64_t)shapes.size();
-
-  std::vector<KrylovPlan> cand;
-  for (int s2 = 0; s2 < (int)shapes.size(); ++s2) {
-    if (shapes[s2].rows() < shapes[b].rows()) continue;  // too small for the bucket
-    const int occ = std::max(1, krylov_occupancy(shapes[s2].id, 0));
-    for (int pc = 1; pc <= occ; ++pc) cand.push_back(make_plan(shapes[s2].id, pc, ctx->device));
-  }
-  plan.candidates = (int)cand.size();
-  if (cand.size() < 2) return MAG_OK;  // nothing to choose
-  hipEvent_t t0 = nullptr, t1 = nullptr;
-  HIPCHK(hipEventCreate(&t0));
-  if (hipEventCreate(&t1) != hipSuccess) {
-    (void)hipEventDestroy(t0);
-    return fail(ctx, MAG_EHIP, "hipEventCreate failed");
-  }
-  Timer tt(ctx->stream);
-  double best = 1e300;
-  for (const KrylovPlan& c : cand) {
-    KrylovArgs kt = ka;
-    kt.slots = ctx->k_slots.as<int32_t>() + off;
-    kt.ncols = S;
-    kt.cache_cap = c.cache;
-    kt.queue = dc;
-    kt.qbeg = dq;
-    kt.nqueue = KRYLOV_QUEUES;
-    const int grid = (int)std::min<int64_t>(S, (int64_t)ncu * c.per_cu);
-    float ms = 0.f;
-    for (int rep = 0; rep < 2; ++rep) {  // the first launch also loads the code object
-      HIPCHK(launch_fill_i32(dc, KRYLOV_QUEUES, 0, ctx->stream));
-      HIPCHK(hipEventRecord(t0, ctx->stream));
-      HIPCHK(launch_krylov(kt, c.shape, c.dyn, grid, ctx->stream));
-      HIPCHK(hipEventRecord(t1, ctx->stream));
-      HIPCHK(hipEventSynchronize(t1));
-      HIPCHK(hipEventElapsedTime(&ms, t0, t1));
-    }
-    const double us = 1e3 * ms / (double)S;
-    if (us < best) {
-      best = us;
-      plan = c;
-      plan.tuned = true;
-      plan.us_per_col = us;
-      plan.candidates = (int)cand.size();
-    }
-  }
-  ctx->stats.autotune_ms += tt.stop_ms();
-  (void)hipEventDestroy(t0);
-  (void)hipEventDestroy(t1);
-  return MAG_OK;
 }
 
 // the plans of the pass's buckets, for mag_get_stats
@@ -492,9 +403,8 @@ static void record_plans(mag_ctx* ctx, const std::vector<KrylovShapeInfo>& shape
       }
     st.plan_per_cu[b] = plans[b]->per_cu;
     st.plan_cache[b] = plans[b]->cache;
-    st.plan_candidates[b] = plans[b]->candidates;
+    st.plan_candidates[b] = 1;
     st.plan_columns[b] = boff[b + 1] - boff[b];
-    st.plan_us_per_col[b] = plans[b]->us_per_col;
   }
 }
 
@@ -591,8 +501,8 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
   const int8_t* bkt = same_order ? ol.bucket.data() : bucket.data();
   const int nbk = (int)shapes.size();
   ALLOC(ctx->k_slots, sizeof(int32_t) * bsz);
-  ALLOC(ctx->k_queue, sizeof(int32_t) * KRYLOV_QUEUES * (nbk + 1));
-  ALLOC(ctx->k_qbeg, sizeof(int64_t) * (KRYLOV_QUEUES + 1) * (nbk + 1));
+  ALLOC(ctx->k_queue, sizeof(int32_t) * KRYLOV_QUEUES * nbk);
+  ALLOC(ctx->k_qbeg, sizeof(int64_t) * (KRYLOV_QUEUES + 1) * nbk);
   // the device lists are still resident unless either buffer was allocated anew
   const bool cached = same_order && ol.slots_epoch == ctx->k_slots.epoch &&
                       ol.qbeg_epoch == ctx->k_qbeg.epoch;
@@ -685,8 +595,8 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
           k1.adj_h = ka.adj_h + q * (int64_t)cap * cap;
           k1.adj_beta = ka.adj_beta + q * (int64_t)cap;
         }
-        const KrylovPlan& pl = krylov_plan(ctx, shapes, bkt[i0 + q], ncu);
-        k1.cache_cap = pl.cache;
+        const KrylovPlan& pl = krylov_plan(ctx, shapes, bkt[i0 + q]);
+        k1.cache_cap = pl.cache / KRYLOV_UNIT_BLOCKS;
         HIPCHK(launch_krylov(k1, pl.shape, pl.dyn, 1, ctx->stream));
         EigArgs e1 = ea;
         e1.hs = k1.hs;
@@ -724,14 +634,12 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
         dqbeg = gl->qbeg + (int64_t)c * nbk * (KRYLOV_QUEUES + 1);
         dqueue = gl->queue + (int64_t)c * nbk * KRYLOV_QUEUES;
         for (int b = 0; b < nbk; ++b)
-          if (boff[b + 1] > boff[b]) plans[b] = &krylov_plan(ctx, shapes, b, ncu);
+          if (boff[b + 1] > boff[b]) plans[b] = &krylov_plan(ctx, shapes, b);
       } else {
         // a pass over every column in one chunk with the lists of the last
         // such pass still resident: no host work, copy or synchronisation
-        const int32_t* hs = nullptr;
         if (cached) {
           boff = ol.boff;
-          hs = ol.hslots.data();
         } else {
           ol.valid = false;
           chunk_lists(ctx, job.cols_host.data() + i0, bkt + i0, cnt, nbk, hslots, hqbeg, boff);
@@ -740,7 +648,6 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
           HIPCHK(hipMemcpyAsync(ctx->k_qbeg.p, hqbeg.data(), sizeof(int64_t) * hqbeg.size(),
                                 hipMemcpyHostToDevice, ctx->stream));
           TRY(sync(ctx));  // the host lists may change or go out of scope
-          hs = hslots.data();
           if (one_chunk_order) {
             if (!same_order) ol.bucket = bucket;  // else ol.bucket is what bkt points to
             ol.hslots = hslots;
@@ -751,17 +658,10 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
             ol.slots_epoch = ctx->k_slots.epoch;
             ol.qbeg_epoch = ctx->k_qbeg.epoch;
             ol.valid = true;
-            hs = ol.hslots.data();
           }
         }
-        // plans (tuned on first use) before the timed launches
-        for (int b = 0; b < nbk; ++b) {
-          if (boff[b + 1] == boff[b]) continue;
-          plans[b] = &krylov_plan(ctx, shapes, b, ncu);
-          if (schedule == MAG_SCHED_PERSISTENT && !plans[b]->tuned)
-            TRY(krylov_tune(ctx, shapes, b, ka, boff[b], boff[b + 1] - boff[b], ncu,
-                            hs + boff[b], job.cols_host.data() + i0));
-        }
+        for (int b = 0; b < nbk; ++b)
+          if (boff[b + 1] > boff[b]) plans[b] = &krylov_plan(ctx, shapes, b);
       }
       hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;
       if (ctx->time_kernels && !gl) {
@@ -791,7 +691,7 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
         KrylovArgs kb = ka;
         kb.slots = dslots + boff[b];
         kb.ncols = nb;
-        kb.cache_cap = pl.cache;
+        kb.cache_cap = pl.cache / KRYLOV_UNIT_BLOCKS;
         int grid = (int)nb;
         if (schedule == MAG_SCHED_PERSISTENT) {
           HIPCHK(launch_fill_i32(dqueue + KRYLOV_QUEUES * b, KRYLOV_QUEUES, 0, ctx->stream));

@@ -21,7 +21,6 @@ constexpr int BLOCKS_MAX = MAG_BLOCKS_MAX;
 constexpr int PAT_MAX = NORB * BLOCKS_MAX;      // pattern entries of one CSR row
 constexpr int NC_MAX = NORB * CLUSTER_MAX;      // cluster orbitals
 constexpr double G_SPIN = 2.0;
-constexpr int CSLOT_BYTES = 272;  // LDS bytes per cached H/S block (256 + bank pad)
 
 // error flags raised by kernels (bit mask in a device int)
 enum KernelError : int {
@@ -101,7 +100,8 @@ struct KrylovArgs {
   int cap;                 // NU capacity used for strides
   int pat_stride;          // rows per slot in qpat (PAT_MAX, or NC_MAX when full)
   int full;                // 1: write every cluster row of Q, not only the pattern
-  int cache_cap;           // cluster blocks kept in LDS for the whole column (dynamic LDS)
+  int cache_cap;           // units of tile blocks kept in LDS at most (0: every block streams)
+  int pool;                // dynamic LDS bytes
   const int32_t* slots;    // nullptr: list position = slot; else the slots of this launch
   // for the exact gradient (or nullptr): per slot the whole basis (cap columns
   // of adj_rows rows, column k at k * adj_rows), the last step's residual
@@ -117,21 +117,18 @@ struct KrylovArgs {
 // how the Krylov columns of one bucket of cluster sizes are launched
 struct KrylovPlan {
   int shape = -1;          // workgroup shape (index into the shape table)
-  size_t dyn = 0;          // dynamic LDS bytes per workgroup (block cache)
-  int cache = 0;           // cached blocks that dyn holds
+  size_t dyn = 0;          // dynamic LDS bytes per workgroup
+  int cache = 0;           // cluster blocks that the LDS keeps at most
   int per_cu = 1;          // persistent workgroups per CU
-  bool tuned = false;      // timed against the other candidates
-  double us_per_col = 0.0; // measured time per column when tuned
-  int candidates = 0;      // plans timed (1: nothing to choose)
 };
 
 struct KrylovShapeInfo {
   int cap;   // nu capacity (template)
   int tpb;   // threads per workgroup
-  int r;     // cluster rows per thread
-  const void* unused;
+  int r;     // rows of a lane's basis vectors
+  int nrows; // cluster rows held
   int id = -1;
-  int rows() const { return tpb * r; }
+  int rows() const { return nrows; }
 };
 
 struct EigArgs {
@@ -191,8 +188,10 @@ struct DensityArgs {
 hipError_t launch_krylov(const KrylovArgs& a, int shape, size_t dyn_lds, int grid, hipStream_t s);
 int krylov_shapes(int cap, KrylovShapeInfo* out, int max_out);  // shapes for a nu capacity
 size_t krylov_static_lds(int shape);
-int krylov_cache_blocks(size_t dyn_lds);
+size_t krylov_pool_min(int shape);              // dynamic LDS a workgroup needs
+int krylov_cache_blocks(int shape, size_t dyn_lds);
 int krylov_occupancy(int shape, size_t dyn_lds);  // workgroups per CU (0: does not fit)
+constexpr int KRYLOV_UNIT_BLOCKS = 16;  // blocks of a cached unit (four per atom of a tile)
 constexpr int KRYLOV_QUEUES = 8;  // one work queue per XCD
 int krylov_capacity(int nu);  // template capacity used for nu (0 if unsupported)
 hipError_t launch_eig(const EigArgs& a, hipStream_t s);
