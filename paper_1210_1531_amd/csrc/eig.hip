@@ -29,9 +29,11 @@
 //     and optionally P_pk = (Q_pat c)_pk d_k on the pattern rows, from which
 //     pass 2 forms rho = 2 P f and pi = 2 P (f eps) (Eq. 2 on the Ritz
 //     spectrum).
+//  With few columns steps 2 and 3 are one kernel, a wave for each column: the
+//  same QL steps, with every rotation applied to Z (in LDS) at once.
 //  A column whose sweeps would overflow the record (or whose QL did not
-//  converge in the lane kernel) is finished by a fallback kernel that runs
-//  the same QL inside one wave with the rotations applied directly.
+//  converge in the lane kernel) is finished by a fallback kernel that does
+//  the same for the listed columns.
 #include <algorithm>
 
 #include "mag_internal.h"
@@ -40,6 +42,14 @@
 namespace mag {
 
 constexpr int ETPB = 64;
+// Up to this many columns the QL runs with a wave for each column, vectors and
+// all (ql_vec_kernel), beyond it with a lane for each column and the vectors
+// replayed.  A wave executes only its own column's rotations, but 64 lanes all
+// the same: with few columns its shorter chain counts (64 columns, nu = 30: QL
+// and vectors 0.22 instead of 0.50 ms), with many the instructions (15,568
+// columns: 2.0 against 1.2 ms).  The two meet at 4,096 columns at every nu
+// from 12 to 48; the bits are the same.
+constexpr int64_t QL_WAVE_COLS = 4096;
 constexpr int QL_MAXIT = 60;  // QL iterations per eigenvalue before giving up
 
 // rotation records: sweep q, plane i at q * eig_sweep_stride + i (planes padded to a
@@ -231,6 +241,43 @@ __global__ __launch_bounds__(ETPB) void tri_kernel(EigArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// The QL steps that the lane kernel and the wave kernel share, written without
+// contraction so that both give the same bits.
+
+// Wilkinson-type shift from the leading 2 x 2 block at l
+__device__ __forceinline__ double ql_shift(double dl, double dl1, double el, double dm) {
+#pragma clang fp contract(off)
+  const double g = (dl1 - dl) / (2.0 * el);
+  const double r = sqrt(fma(g, g, 1.0));
+  return dm - dl + el / (g + copysign(r, g));
+}
+
+// the rotation of the plane (i, i+1) that carries the bulge (g, sn, cs, p) on
+struct QlRot {
+  double sn, cs, g, p;
+  double d1, e1;  // new d[i+1], e[i+1]
+  bool bad;       // |(f, g)| = 0: only by underflow, the sweep ends with the identity
+};
+__device__ __forceinline__ QlRot ql_rotate(double di, double di1, double ei, double sn, double cs,
+                                           double g, double p) {
+#pragma clang fp contract(off)
+  QlRot o;
+  const double f = sn * ei, b = cs * ei;
+  const double q = fma(f, f, g * g);
+  o.bad = !(q > 0.0);
+  const double rinv = o.bad ? 0.0 : rsqrt(o.bad ? 1.0 : q);
+  o.sn = f * rinv;
+  o.cs = o.bad ? 1.0 : g * rinv;
+  const double g1 = di1 - p;
+  const double r1 = fma(di - g1, o.sn, 2.0 * o.cs * b);
+  o.p = o.sn * r1;
+  o.g = fma(o.cs, r1, -b);
+  o.e1 = q * rinv;
+  o.d1 = g1 + o.p;
+  return o;
+}
+
+// ---------------------------------------------------------------------------
 // 2. QL on the tridiagonal, one lane per column, rotations recorded per sweep.
 // The lanes of a wave sit at different eigenvalues l and sweep lengths, so
 // the loop is flattened into trips: in each trip a lane either deflates
@@ -285,7 +332,6 @@ __global__ __launch_bounds__(ETPB) void ql_kernel(EigArgs a) {
       sweep = false;
     }
     if (__builtin_amdgcn_ballot_w64(sweep) == 0) continue;
-    // Wilkinson-type shift from the leading 2 x 2 block at l
     double dl = 0.0, dl1 = 0.0, el = 1.0;
 #pragma unroll
     for (int t = 0; t < NM; ++t) {
@@ -293,9 +339,7 @@ __global__ __launch_bounds__(ETPB) void ql_kernel(EigArgs a) {
       el = (sweep && t == l) ? e[t] : el;
       dl1 = (t == l + 1) ? d[t] : dl1;
     }
-    double g = (dl1 - dl) / (2.0 * el);
-    double r = sqrt(fma(g, g, 1.0));
-    g = dm - dl + el / (g + copysign(r, g));
+    double g = ql_shift(dl, dl1, el, dm);
     double sn = 1.0, cs = 1.0, p = 0.0;
     bool under = false;
     int cnt = 0;
@@ -306,29 +350,18 @@ __global__ __launch_bounds__(ETPB) void ql_kernel(EigArgs a) {
     for (int i = NM - 2; i >= 0; --i) {
       const bool act = sweep && i < ms && i >= l && !under;
       if (__builtin_amdgcn_ballot_w64(act) == 0) continue;
-      const double f = sn * e[i], b = cs * e[i];
-      // r = |(f, g)|; r == 0 only by underflow, and then the identity rotation
-      // (sn, cs) = (0, 1) gives d[i+1] -= p, and the sweep ends
-      const double q = fma(f, f, g * g);
-      const bool bad = !(q > 0.0);
-      const double rinv = bad ? 0.0 : rsqrt(bad ? 1.0 : q);
-      const double sn1 = f * rinv;
-      const double cs1 = bad ? 1.0 : g * rinv;
-      const double g1 = d[i + 1] - p;
-      const double r1 = fma(d[i] - g1, sn1, 2.0 * cs1 * b);
-      const double p1 = sn1 * r1;
-      const double g2 = fma(cs1, r1, -b);
-      if (act) rec[nsw * SWS + i] = make_double2(sn1, cs1);
-      e[i + 1] = act ? ((i + 1 == ms) ? 0.0 : q * rinv) : e[i + 1];
-      d[i + 1] = act ? g1 + p1 : d[i + 1];
-      const bool fin = act && i == l && !bad;
-      d[i] = fin ? d[i] - p1 : d[i];
-      e[i] = fin ? g2 : e[i];
-      sn = act ? sn1 : sn;
-      cs = act ? cs1 : cs;
-      p = act ? p1 : p;
-      g = act ? g2 : g;
-      under = under || (act && bad);
+      const QlRot o = ql_rotate(d[i], d[i + 1], e[i], sn, cs, g, p);
+      if (act) rec[nsw * SWS + i] = make_double2(o.sn, o.cs);
+      e[i + 1] = act ? ((i + 1 == ms) ? 0.0 : o.e1) : e[i + 1];
+      d[i + 1] = act ? o.d1 : d[i + 1];
+      const bool fin = act && i == l && !o.bad;
+      d[i] = fin ? d[i] - o.p : d[i];
+      e[i] = fin ? o.g : e[i];
+      sn = act ? o.sn : sn;
+      cs = act ? o.cs : cs;
+      p = act ? o.p : p;
+      g = act ? o.g : g;
+      under = under || (act && o.bad);
       cnt += act ? 1 : 0;
     }
     if (sweep) {
@@ -343,83 +376,69 @@ __global__ __launch_bounds__(ETPB) void ql_kernel(EigArgs a) {
   if (status != 0) a.fb_list[atomicAdd(a.fb_count, 1)] = (int32_t)slot;
 }
 
-// the same QL inside one wave, rotations applied to the row of Z held by each lane
+// lane `src` (uniform) of v, in every lane
+__device__ __forceinline__ double lane_of(double v, int src) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
+                          __builtin_amdgcn_readlane(__double2loint(v), src));
+}
+
+// the same QL inside one wave: lane t holds d[t] and e[t], every lane carries the
+// bulge, and row `lane` of Z (Z[t * (NM + 1) + lane] in LDS; the lanes past NM share
+// the pad) is rotated along the way, its running element in a register.  Only
+// the rotations of the sweep are executed, one after the other: their serial
+// chain (about 200 cycles each) is what this costs.
 template <int NM>
-__device__ __forceinline__ bool ql_wave(const double* tr, int n, double* z, double* ev, int lane) {
-  double d[NM], e[NM];
+__device__ __forceinline__ bool ql_wave(const double* tr, int n, double* Z, double* ev, int lane) {
+  constexpr int LD = NM + 1;
+  double d = lane < n ? tr[lane] : 0.0, e = lane < n ? tr[NM + lane] : 0.0;
+  double* zr = Z + min(lane, NM);
 #pragma unroll
-  for (int t = 0; t < NM; ++t) {
-    d[t] = (t < n) ? tr[t] : 0.0;
-    e[t] = (t < n) ? tr[NM + t] : 0.0;
-  }
+  for (int t = 0; t < NM; ++t) zr[t * LD] = (t == lane) ? 1.0 : 0.0;
   bool ok = true;
-  for (int l = 0; l < n && ok; ++l) {
-    for (int iter = 0;; ++iter) {
-      int ms = n - 1;
-#pragma unroll
-      for (int t = NM - 2; t >= 0; --t) {
-        if (t >= l && t < n - 1) {
-          if (fabs(e[t]) <= 0x1p-52 * (fabs(d[t]) + fabs(d[t + 1]))) ms = t;
-        }
-      }
-      ms = __builtin_amdgcn_readfirstlane(ms);
-      if (ms == l) break;
-      if (iter >= QL_MAXIT) {
-        ok = false;
+  int l = 0, iter = 0;
+  while (l < n) {
+    // ms: the first negligible subdiagonal at or after l, n - 1 if none
+    const double dn = __shfl_down(d, 1, 64);
+    const uint64_t neg = __builtin_amdgcn_ballot_w64(
+        lane >= l && lane < n - 1 && fabs(e) <= 0x1p-52 * (fabs(d) + fabs(dn)));
+    const int ms = neg ? (int)__builtin_ctzll(neg) : n - 1;
+    if (ms == l) {
+      ++l;
+      iter = 0;
+      continue;
+    }
+    if (iter++ >= QL_MAXIT) {
+      ok = false;
+      break;
+    }
+    double di1 = lane_of(d, ms);
+    double g = ql_shift(lane_of(d, l), lane_of(d, l + 1), lane_of(e, l), di1);
+    double sn = 1.0, cs = 1.0, p = 0.0;
+    double zf = zr[ms * LD], zi = zr[(ms - 1) * LD];
+    int i = ms - 1;
+    for (;; --i) {
+      const double di = lane_of(d, i), zn = zr[max(i - 1, 0) * LD];
+      const QlRot o = ql_rotate(di, di1, lane_of(e, i), sn, cs, g, p);
+      d = (lane == i + 1) ? o.d1 : d;
+      e = (lane == i + 1) ? (i + 1 == ms ? 0.0 : o.e1) : e;
+      zr[(i + 1) * LD] = fma(o.sn, zi, o.cs * zf);
+      zf = fma(o.cs, zi, -o.sn * zf);
+      zi = zn;
+      sn = o.sn;
+      cs = o.cs;
+      g = o.g;
+      p = o.p;
+      if (__builtin_amdgcn_readfirstlane((int)o.bad)) break;
+      if (i == l) {
+        d = (lane == l) ? di - p : d;
+        e = (lane == l) ? g : e;
         break;
       }
-      double dl = 0.0, dl1 = 0.0, el = 0.0, dm = 0.0;
-#pragma unroll
-      for (int t = 0; t < NM; ++t) {
-        if (t == l) {
-          dl = d[t];
-          el = e[t];
-        }
-        if (t == l + 1) dl1 = d[t];
-        if (t == ms) dm = d[t];
-      }
-      double g = (dl1 - dl) / (2.0 * el);
-      double r = sqrt(fma(g, g, 1.0));
-      g = dm - dl + el / (g + copysign(r, g));
-      double sn = 1.0, cs = 1.0, p = 0.0;
-      bool under = false;
-#pragma unroll
-      for (int i = NM - 2; i >= 0; --i) {
-        if (i >= ms) continue;
-        if (i < l || under) break;
-        const double f = sn * e[i], b = cs * e[i];
-        const double q = fma(f, f, g * g);
-        const bool bad = !(q > 0.0);
-        const double rinv = bad ? 0.0 : rsqrt(q);
-        r = q * rinv;
-        e[i + 1] = r;
-        sn = f * rinv;
-        cs = bad ? 1.0 : g * rinv;
-        g = d[i + 1] - p;
-        r = fma(d[i] - g, sn, 2.0 * cs * b);
-        p = sn * r;
-        d[i + 1] = g + p;
-        g = fma(cs, r, -b);
-        const double zf = z[i + 1];
-        z[i + 1] = fma(sn, z[i], cs * zf);
-        z[i] = fma(cs, z[i], -sn * zf);
-        under = __builtin_amdgcn_readfirstlane((int)bad) != 0;
-      }
-#pragma unroll
-      for (int t = 0; t < NM; ++t) {
-        if (!under && t == l) {
-          d[t] -= p;
-          e[t] = g;
-        }
-        if (t == ms) e[t] = 0.0;
-      }
+      di1 = di;
     }
+    zr[i * LD] = zf;
   }
-  if (lane == 0) {
-#pragma unroll
-    for (int t = 0; t < NM; ++t)
-      if (t < n) ev[t] = d[t];
-  }
+  if (lane < n) ev[lane] = d;
   return ok;
 }
 
@@ -433,7 +452,8 @@ __device__ __forceinline__ bool ql_wave(const double* tr, int n, double* z, doub
 typedef const __attribute__((address_space(4))) double kdouble;
 typedef const __attribute__((address_space(4))) int32_t kint;
 
-template <int NM, bool FB>
+// WQL: the QL runs here too, inside the wave
+template <int NM, bool WQL>
 __device__ __forceinline__ void vectors_column(const EigArgs& a, int64_t slot, double* sm) {
   constexpr int LD = NM + 1;
   const int lane = threadIdx.x;
@@ -449,7 +469,7 @@ __device__ __forceinline__ void vectors_column(const EigArgs& a, int64_t slot, d
     if (lane == 0) a.nu_eff_out[oi] = 0;
     return;
   }
-  double* T = sm;            // NM x LD: rows of Z, read back as columns
+  double* T = sm;            // NM x LD: Z by columns (row i at t * LD + i)
   double* ev = T + NM * LD;  // eigenvalues (unsorted)
   // L by columns (1 / L_ii on the diagonal), the reflector rows, the
   // tridiagonal's scratch: all zero past n
@@ -458,10 +478,11 @@ __device__ __forceinline__ void vectors_column(const EigArgs& a, int64_t slot, d
   kdouble* tr = (kdouble*)(a.trid + slot * (int64_t)(4 * NM));
 
   // ---- Z_T: rows of the identity, rotated (lane i holds row i)
-  double z[NM];
+  double y[NM];
+  if (!WQL) {
+    double z[NM];
 #pragma unroll
-  for (int t = 0; t < NM; ++t) z[t] = (t == lane) ? 1.0 : 0.0;
-  if (!FB) {
+    for (int t = 0; t < NM; ++t) z[t] = (t == lane) ? 1.0 : 0.0;
     const int nsw = a.qlst[slot];
     constexpr int SWS = eig_sweep_stride(NM);
     kdouble* rec = (kdouble*)(a.rot + slot * (int64_t)(2 * a.rec_cap));  // (sn, cs) pairs
@@ -497,13 +518,13 @@ __device__ __forceinline__ void vectors_column(const EigArgs& a, int64_t slot, d
       }
     }
     if (lane < n) ev[lane] = a.evu[slot * (int64_t)NM + lane];
-  } else {
-    if (!ql_wave<NM>(a.trid + slot * (int64_t)(4 * NM), n, z, ev, lane) && lane == 0)
-      atomicOr(a.err, (int)KERR_NOCONV);
-  }
-  if (lane < NM) {
+    if (lane < NM) {
 #pragma unroll
-    for (int t = 0; t < NM; ++t) T[lane * LD + t] = z[t];
+      for (int t = 0; t < NM; ++t) T[t * LD + lane] = z[t];
+    }
+  } else {
+    if (!ql_wave<NM>(a.trid + slot * (int64_t)(4 * NM), n, T, ev, lane) && lane == 0)
+      atomicOr(a.err, (int)KERR_NOCONV);
   }
   __syncthreads();
   // ---- rank of eigenvalue `lane` (ascending, ties by index)
@@ -518,9 +539,8 @@ __device__ __forceinline__ void vectors_column(const EigArgs& a, int64_t slot, d
     }
   }
   // ---- column `lane` of Z_T (zero past n for lanes below n)
-  double y[NM];
 #pragma unroll
-  for (int t = 0; t < NM; ++t) y[t] = (lane < NM) ? T[t * LD + lane] : 0.0;
+  for (int t = 0; t < NM; ++t) y[t] = (lane < NM) ? T[lane * LD + t] : 0.0;
   // ---- y = P_0 P_1 ... P_{n-3} y
   for (int k = n - 3; k >= 0; --k) {
     const double beta = tr[2 * NM + k];
@@ -632,6 +652,13 @@ __global__ __launch_bounds__(ETPB) void vec_kernel(EigArgs a) {
   vectors_column<NM, false>(a, slot, sm);
 }
 
+// QL and vectors of every column, one wave each
+template <int NM>
+__global__ __launch_bounds__(ETPB) void ql_vec_kernel(EigArgs a) {
+  extern __shared__ double sm[];
+  if ((int64_t)blockIdx.x < a.ncols) vectors_column<NM, true>(a, blockIdx.x, sm);
+}
+
 template <int NM>
 __global__ __launch_bounds__(ETPB) void vec_fallback_kernel(EigArgs a) {
   extern __shared__ double sm[];
@@ -648,6 +675,10 @@ static hipError_t launch_eig_nm(const EigArgs& a, hipStream_t s) {
   const size_t lds1 = (size_t)NM * (NM + 1) * sizeof(double);
   const size_t lds3 = (size_t)NM * (NM + 1) * sizeof(double) + NM * sizeof(double) + NM * sizeof(int);
   hipLaunchKernelGGL(tri_kernel<NM>, dim3(nb), dim3(ETPB), lds1, s, a);
+  if (a.ncols <= QL_WAVE_COLS && a.sweep_cap >= eig_sweep_cap(NM)) {
+    hipLaunchKernelGGL(ql_vec_kernel<NM>, dim3(nb), dim3(ETPB), lds3, s, a);
+    return hipGetLastError();
+  }
   hipError_t e = launch_fill_i32(a.fb_count, 1, 0, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(ql_kernel<NM>, dim3((nb + ETPB - 1) / ETPB), dim3(ETPB), 0, s, a);
