@@ -1401,18 +1401,23 @@ int mag_get_clusters(mag_ctx* ctx, int64_t* clus_ptr, int32_t* clus_atoms, int64
 // forward
 // ---------------------------------------------------------------------------
 // bisection launches for brackets up to 1e7 eV wide at tolerance tol (five
-// levels per launch); launches after convergence return at once
+// levels per launch, but for one that a poor guess of the root may cost);
+// launches after convergence return at once
 static int mu_rounds(double tol) {
   const int levels = (int)std::ceil(std::log2(1e7 / tol)) + 2;
-  return (levels + mu_levels_per_round() - 1) / mu_levels_per_round();
+  return (levels + mu_levels_per_round() - 1) / mu_levels_per_round() + 1;
 }
 
 static int mu_grid(const mag_ctx* ctx) {
   // about 16 Ritz terms per thread, at most two blocks per CU: a launch is
   // short, and its tail (the last block reading every block's partials
   // back from L2) grows with the grid, so fewer, fuller blocks finish first
-  // (0.58 -> 0.37 ms for the ten launches of a 15,568-column solve)
-  return (int)std::min<int64_t>(512, std::max<int64_t>(1, (ctx->M * ctx->nu + 4095) / 4096));
+  // (0.58 -> 0.37 ms for the ten launches of a 15,568-column solve).  A small
+  // system spreads over more blocks, one term per thread: up to 128 blocks the
+  // tail costs less than the terms
+  const int64_t terms = ctx->M * ctx->nu;
+  const int64_t spread = std::min<int64_t>(128, (terms + 255) / 256);
+  return (int)std::min<int64_t>(512, std::max<int64_t>(spread, (terms + 4095) / 4096));
 }
 
 // enqueue the bisection for mu and the energy sums (no host synchronisation)

@@ -75,7 +75,9 @@ struct MuState {
   int err;
   unsigned counter;
   double emin, emax;
-  double pad[4];
+  int guess;        // the next round's points are pts (else the interval tree)
+  int tree;         // no further guesses
+  double pts[32];
 };
 
 struct KrylovArgs {

@@ -8,7 +8,14 @@
 // halvings (the binary tree of intervals below the current bracket, each node's
 // midpoint formed exactly as plain bisection would) and then walks the tree
 // with the plain rule; the result is the same sequence of brackets as plain
-// bisection, five levels per launch.  Reductions are deterministic: fixed
+// bisection, five levels per launch.  Once the bracket is narrow on the kT
+// scale N(mu) is smooth inside it: the root is guessed by inverse cubic
+// interpolation of the points evaluated last and the next 31 points are placed
+// about the guess, in geometric distances.  N is monotone, so the points next
+// to the root decide every midpoint outside them, and plain bisection's
+// sequence goes on until a midpoint falls between the two: the last 40 or so
+// halvings take three launches or four instead of eight.  A guess that decides fewer than five levels is the
+// last one.  Reductions are deterministic: fixed
 // grid-stride partition, fixed in-block order, and the last block to finish
 // sums the per-block partials in block order.
 #include "mag_internal.h"
@@ -201,7 +208,12 @@ __global__ __launch_bounds__(MTPB) void mu_round_kernel(const double* eps, const
   // with the bracket narrow on the kT scale, f at every point follows from one
   // exponential per term: exp((e - mu_p)/kT) = exp((e - mu0)/kT) exp((mu0 - mu_p)/kT)
   const bool factored = (hi0 - lo0) <= 600.0 * kT;
-  if (tid < MPTS) {
+  const bool guess = st->guess != 0;
+  if (guess && tid < MPTS) {
+    const double pt = st->pts[tid];
+    s_pts[tid] = pt;
+    s_cp[tid] = exp((mu0 - pt) / kT);
+  } else if (tid < MPTS) {
     // node n = tid + 1 of the interval tree: walk from the root
     const int n = tid + 1;
     const int depth = 31 - __clz(n);
@@ -265,10 +277,35 @@ __global__ __launch_bounds__(MTPB) void mu_round_kernel(const double* eps, const
     const double tot = block_sum_partials(partials, (int)gridDim.x, 32, 0.0, OpAdd{}, s_tmp);
     if (tid < 32) s_N[tid] = tot;
     __syncthreads();
-    if (tid == 0) {
-      double lo = lo0, hi = hi0;
-      int n = 1, lev = st->levels, done = 0;
-      const double ne = st->ne, tol = st->tol;
+    if (tid >= 64) return;
+    // (every lane of the first wave does the same, lane 0 writes)
+    double lo = lo0, hi = hi0;
+    int lev = st->levels, done = 0;
+    const double ne = st->ne, tol = st->tol;
+    // the points next to the root: N < N_e up to a1, N >= N_e from b1 on
+    double a1 = lo, b1 = hi, a2 = lo, b2 = hi, ya1 = 0.0, yb1 = 0.0, ya2 = 0.0, yb2 = 0.0;
+    bool ha1 = false, hb1 = false, ha2 = false, hb2 = false;  // evaluated, not the bracket's end
+#pragma unroll
+    for (int p = 0; p < MPTS; ++p) {
+      const double x = s_pts[p];
+      if (s_N[p] >= ne && x < b1) b1 = x;
+    }
+#pragma unroll
+    for (int p = 0; p < MPTS; ++p) {
+      const double x = s_pts[p];
+      if (s_N[p] < ne && x < b1 && x > a1) a1 = x;
+    }
+    if (guess) {
+      // (bounded: a tolerance below the spacing of doubles never ends it)
+      for (int l = 0; l < 64 && hi - lo > tol; ++l) {
+        const double mid = lo + (hi - lo) / 2.0;
+        if (mid <= a1) lo = mid;
+        else if (mid >= b1) hi = mid;
+        else break;
+        ++lev;
+      }
+    } else {
+      int n = 1;
       for (int l = 0; l < MLEV; ++l) {
         if (!(hi - lo > tol)) {
           done = 1;
@@ -284,12 +321,56 @@ __global__ __launch_bounds__(MTPB) void mu_round_kernel(const double* eps, const
         }
         ++lev;
       }
-      if (!(hi - lo > tol)) done = 1;
+    }
+    if (!(hi - lo > tol)) done = 1;
+    // the next round's points: the tree, or points about a guess of the root,
+    // unless guesses have brought less than a tree before
+    const bool tree = st->tree != 0 || (guess && lev < st->levels + MLEV);
+    const bool next = !done && !tree && hi - lo <= 2.0 * kT;
+    if (next) {
+#pragma unroll
+      for (int p = 0; p < MPTS; ++p) {
+        const double x = s_pts[p], y = s_N[p] - ne;
+        if (x == a1) ya1 = y, ha1 = true;
+        if (x == b1) yb1 = y, hb1 = true;
+        if (x < a1 && (!ha2 || x > a2)) a2 = x, ya2 = y, ha2 = true;
+        if (x > b1 && (!hb2 || x < b2)) b2 = x, yb2 = y, hb2 = true;
+      }
+      double g = a1 + (b1 - a1) / 2.0, err = b1 - a1;
+      if (ha1 && hb1 && ha2 && hb2 && ya2 < ya1 && ya1 < yb1 && yb1 < yb2) {
+        // N(mu) interpolated inversely: the line through the two, Neville's
+        // cubic through all four, both at N_e
+        const double l0 = a1 - ya1 * ((b1 - a1) / (yb1 - ya1));
+        const double m0 = a2 - ya2 * ((a1 - a2) / (ya1 - ya2));
+        const double m2 = b1 - yb1 * ((b2 - b1) / (yb2 - yb1));
+        const double q0 = (yb1 * m0 - ya2 * l0) / (yb1 - ya2);
+        const double q1 = (yb2 * l0 - ya1 * m2) / (yb2 - ya1);
+        const double c0 = (yb2 * q0 - ya2 * q1) / (yb2 - ya2);
+        if (c0 > a1 && c0 < b1) {
+          g = c0;
+          err = fabs(c0 - l0);
+        }
+      }
+      // fifteen points on each side of the guess at distances from smin to the
+      // known bracket's width, a constant ratio apart, and plain bisection's
+      // next midpoint
+      const double smax = b1 - a1;
+      const double smin = fmax(fmax(tol / 64.0, 1e-5 * err), 1e-15 * fabs(g));
+      const double lr = log2(fmax(smax / smin, 1.0)) * (1.0 / 14.0);
+      if (tid < MPTS) {
+        const double sd = smin * exp2(lr * (double)(tid >> 1));
+        const double mid = lo + (hi - lo) / 2.0;
+        st->pts[tid] = tid == MPTS - 1 ? mid : ((tid & 1) ? g + sd : g - sd);
+      }
+    }
+    if (tid == 0) {
       st->lo = lo;
       st->hi = hi;
       st->levels = lev;
       st->done = done;
       st->mu = lo + (hi - lo) / 2.0;
+      st->guess = next ? 1 : 0;
+      st->tree = tree ? 1 : 0;
       st->counter = 0;
     }
   }
