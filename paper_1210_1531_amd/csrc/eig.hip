@@ -46,7 +46,7 @@ constexpr int ETPB = 64;
 // all (ql_vec_kernel), beyond it with a lane for each column and the vectors
 // replayed.  A wave executes only its own column's rotations, but 64 lanes all
 // the same: with few columns its shorter chain counts (64 columns, nu = 30: QL
-// and vectors 0.22 instead of 0.50 ms), with many the instructions (15,568
+// and vectors 0.17 instead of 0.50 ms), with many the instructions (15,568
 // columns: 2.0 against 1.2 ms).  The two meet at 4,096 columns at every nu
 // from 12 to 48; the bits are the same.
 constexpr int64_t QL_WAVE_COLS = 4096;
@@ -265,7 +265,11 @@ __device__ __forceinline__ QlRot ql_rotate(double di, double di1, double ei, dou
   const double f = sn * ei, b = cs * ei;
   const double q = fma(f, f, g * g);
   o.bad = !(q > 0.0);
-  const double rinv = o.bad ? 0.0 : rsqrt(o.bad ? 1.0 : q);
+  // 1 / sqrt(q) from the hardware estimate y by the third-order step
+  // y (1 + r / 2 + 3 r^2 / 8), r = 1 - q y^2
+  const double y = __builtin_amdgcn_rsq(q);
+  const double r = fma(-(q * y), y, 1.0);
+  const double rinv = o.bad ? 0.0 : fma(y * r, fma(r, 0.375, 0.5), y);
   o.sn = f * rinv;
   o.cs = o.bad ? 1.0 : g * rinv;
   const double g1 = di1 - p;
@@ -386,7 +390,7 @@ __device__ __forceinline__ double lane_of(double v, int src) {
 // bulge, and row `lane` of Z (Z[t * (NM + 1) + lane] in LDS; the lanes past NM share
 // the pad) is rotated along the way, its running element in a register.  Only
 // the rotations of the sweep are executed, one after the other: their serial
-// chain (about 200 cycles each) is what this costs.
+// chain is what this costs (about 500 cycles each, 0.12 ms at nu = 30).
 template <int NM>
 __device__ __forceinline__ bool ql_wave(const double* tr, int n, double* Z, double* ev, int lane) {
   constexpr int LD = NM + 1;
@@ -415,28 +419,34 @@ __device__ __forceinline__ bool ql_wave(const double* tr, int n, double* Z, doub
     double g = ql_shift(lane_of(d, l), lane_of(d, l + 1), lane_of(e, l), di1);
     double sn = 1.0, cs = 1.0, p = 0.0;
     double zf = zr[ms * LD], zi = zr[(ms - 1) * LD];
-    int i = ms - 1;
-    for (;; --i) {
-      const double di = lane_of(d, i), zn = zr[max(i - 1, 0) * LD];
+    double* zp = zr + (ms - 1) * LD;  // plane i's first element
+    int up = lane - ms;               // lane - (i + 1)
+    bool bad = false;
+    for (int i = ms - 1;; --i) {
+      const double di = lane_of(d, i), zn = zp[i > l ? -LD : 0];
       const QlRot o = ql_rotate(di, di1, lane_of(e, i), sn, cs, g, p);
-      d = (lane == i + 1) ? o.d1 : d;
-      e = (lane == i + 1) ? (i + 1 == ms ? 0.0 : o.e1) : e;
-      zr[(i + 1) * LD] = fma(o.sn, zi, o.cs * zf);
+      d = (up == 0) ? o.d1 : d;
+      e = (up == 0) ? o.e1 : e;
+      zp[LD] = fma(o.sn, zi, o.cs * zf);
       zf = fma(o.cs, zi, -o.sn * zf);
       zi = zn;
       sn = o.sn;
       cs = o.cs;
       g = o.g;
       p = o.p;
-      if (__builtin_amdgcn_readfirstlane((int)o.bad)) break;
-      if (i == l) {
-        d = (lane == l) ? di - p : d;
-        e = (lane == l) ? g : e;
-        break;
-      }
       di1 = di;
+      // (uniform: the same values in every lane)
+      bad = __builtin_amdgcn_ballot_w64(o.bad) != 0;
+      if (bad || i == l) break;
+      zp -= LD;
+      ++up;
     }
-    zr[i * LD] = zf;
+    *zp = zf;
+    e = (lane == ms) ? 0.0 : e;
+    if (!bad) {
+      d = (lane == l) ? di1 - p : d;
+      e = (lane == l) ? g : e;
+    }
   }
   if (lane < n) ev[lane] = d;
   return ok;
