@@ -1870,10 +1870,7 @@ int mag_cocg_columns(mag_ctx* ctx, const int32_t* cols, int64_t n, const double*
   ca.G = dst;
   ca.iters = pit;
   ca.err = ctx->errflag.as<int32_t>();
-  for (int q0 = 0; q0 < nz; q0 += COCG_NZ) {
-    ca.q0 = q0;
-    HIPCHK(launch_cocg(ca, ctx->stream));
-  }
+  HIPCHK(launch_cocg(ca, ctx->stream));
   TRY(take_errors(ctx, "mag_cocg_columns"));
   ctx->stats.t_cocg_ms = tm.stop_ms();
   if (mem_kind == MAG_HOST)

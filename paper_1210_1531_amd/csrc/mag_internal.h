@@ -299,8 +299,7 @@ hipError_t launch_icohp(const SKModelDev& m, const double* pos, int64_t n, int64
 hipError_t launch_pair_rep(const SKModelDev& m, const double* pos, int64_t n, const double cell[3],
                            const int32_t* bptr, const int32_t* bcol, double phi0, double mexp,
                            double* e, double* F, hipStream_t s);
-// COCG Green's-function columns (cocg.hip): energies per launch
-constexpr int COCG_NZ = 4;
+// COCG Green's-function columns (cocg.hip)
 struct CocgArgs {
   const int32_t* cols;  // global column ids
   int64_t ncols;
@@ -311,7 +310,7 @@ struct CocgArgs {
   const double* bval;  // block values, H then S per 4x4 block
   const double* z;     // all energies (re, im)
   int nz;              // number of energies
-  int q0;              // first energy of this launch
+  int q0;              // first energy of this launch (set by the launcher)
   double tol;          // |r| <= tol (|b| = 1)
   int max_iter;
   const int64_t* off;  // output row offsets per column (n + 1)
