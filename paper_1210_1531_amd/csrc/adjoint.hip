@@ -773,13 +773,18 @@ __global__ __launch_bounds__(64) void adj_prep_kernel(const double* cvec, const 
 }
 
 // ---------------------------------------------------------------------------
-// stage 3: F_I = sum over the clusters holding I of their parts for I
+// stage 3: F_I = sum over the clusters holding I of their parts for I.  One wave
+// per atom, a lane per cluster: each finds I by bisection, a chain of dependent
+// reads, so with a thread per atom the chains of its 150 clusters followed one
+// another (3,892 atoms 0.56 ms, 61 atoms 0.085 ms; a wave each 0.03 and 0.01 ms).
+// The lanes' sums are added in a fixed order.
 __global__ void gather_forces_kernel(const int64_t* clus_ptr, const int32_t* clus_atoms,
                                      int64_t n, const double* fJ, double* F) {
-  const int64_t I = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t I = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   if (I >= n) return;
+  const int lane = threadIdx.x & 63;
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int64_t q = clus_ptr[I]; q < clus_ptr[I + 1]; ++q) {
+  for (int64_t q = clus_ptr[I] + lane; q < clus_ptr[I + 1]; q += 64) {
     const int J = clus_atoms[q];  // I lies in the cluster of J (the relation is symmetric)
     const int64_t b = clus_ptr[J];
     int lo = 0, hi = (int)(clus_ptr[J + 1] - b) - 1, pos = -1;
@@ -799,7 +804,10 @@ __global__ void gather_forces_kernel(const int64_t* clus_ptr, const int32_t* clu
     }
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c) F[3 * I + c] = acc[c];
+  for (int c = 0; c < 3; ++c) {
+    const double t = wave_allreduce(acc[c]);
+    if (lane == c) F[3 * I + c] = t;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -902,7 +910,7 @@ hipError_t launch_adj_prep(const double* cvec, const double* cdg, const int32_t*
 hipError_t launch_gather_forces(const int64_t* clus_ptr, const int32_t* clus_atoms, int64_t n,
                                 const double* fJ, double* F, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(gather_forces_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL(gather_forces_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s,
                      clus_ptr, clus_atoms, n, fJ, F);
   return hipGetLastError();
 }
