@@ -37,11 +37,12 @@
 //     and atom A's force from column j is sum_B G_AB.  The basis and Z are
 //     staged through LDS a few columns at a time.
 //
-// One workgroup owns one atom at a time and runs its four columns; the
-// atom's force parts on its cluster atoms (fJ, indexed like the cluster
-// list) are summed over the columns in LDS, and gather_forces_kernel adds,
-// for every atom I, the parts that the clusters holding I computed for it
-// (deterministic order).  A column whose Krylov space breaks down is
+// One workgroup owns one atom at a time and runs its four columns (of a small
+// system one column, so that its few atoms fill the chip); the force parts on
+// the cluster atoms (fJ, indexed like the cluster list) are summed over the
+// columns in LDS (of a small system by the gather, in the same order), and
+// gather_forces_kernel adds, for every atom I, the parts that the clusters
+// holding I computed for it (deterministic order).  A column whose Krylov space breaks down is
 // differentiated at its dimension nu_eff.
 #include <algorithm>
 
@@ -248,7 +249,8 @@ __device__ __forceinline__ void load_column(const double (&qv)[R][NU], double (&
     }
 }
 
-template <int NU, int R, int KTPB>
+// SPLIT: a workgroup takes one column of an atom, else an atom's four
+template <int NU, int R, int KTPB, bool SPLIT>
 __global__ __launch_bounds__(KTPB) void adjoint_kernel(AdjointArgs a) {
   constexpr int NCH = (NU + 7) / 8;
   constexpr int RED = 8 * NCH + 8;
@@ -296,9 +298,11 @@ __global__ __launch_bounds__(KTPB) void adjoint_kernel(AdjointArgs a) {
   for (;;) {
     if (tid == 0) s_misc[0] = atomicAdd(a.counter, 1);
     __syncthreads();
-    const int64_t ia = s_misc[0];
+    const int64_t item = s_misc[0];
     __syncthreads();
+    const int64_t ia = SPLIT ? item / NORB : item;
     if (ia >= a.natoms) break;
+    const int al0 = SPLIT ? (int)(item % NORB) : 0;
     const int j0 = a.cols[4 * ia];
     const int J = j0 >> 2;
     bool ok = (j0 & 3) == 0;
@@ -397,7 +401,7 @@ __global__ __launch_bounds__(KTPB) void adjoint_kernel(AdjointArgs a) {
       }
     }
 
-    for (int alpha = 0; alpha < NORB; ++alpha) {
+    for (int alpha = al0; alpha < (SPLIT ? al0 + 1 : NORB); ++alpha) {
       const int64_t slot = 4 * ia + alpha;
       // ---- the forward pass's Krylov data of this column: its basis (in
       // registers, as the forward holds it), h, beta and the last residual
@@ -675,7 +679,8 @@ __global__ __launch_bounds__(KTPB) void adjoint_kernel(AdjointArgs a) {
       __syncthreads();
     }
     // ---- the atom's parts on its cluster atoms
-    for (int idx = tid; idx < 3 * nat; idx += KTPB) a.fJ[3 * c0 + idx] = s_f[idx];
+    double* fJ = a.fJ + (SPLIT ? al0 * a.fstride : 0) + 3 * c0;
+    for (int idx = tid; idx < 3 * nat; idx += KTPB) fJ[idx] = s_f[idx];
     __syncthreads();
   }
 }
@@ -779,7 +784,8 @@ __global__ __launch_bounds__(64) void adj_prep_kernel(const double* cvec, const 
 // another (3,892 atoms 0.56 ms, 61 atoms 0.085 ms; a wave each 0.03 and 0.01 ms).
 // The lanes' sums are added in a fixed order.
 __global__ void gather_forces_kernel(const int64_t* clus_ptr, const int32_t* clus_atoms,
-                                     int64_t n, const double* fJ, double* F) {
+                                     int64_t n, const double* fJ, int parts, int64_t fstride,
+                                     double* F) {
   const int64_t I = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   if (I >= n) return;
   const int lane = threadIdx.x & 63;
@@ -800,7 +806,11 @@ __global__ void gather_forces_kernel(const int64_t* clus_ptr, const int32_t* clu
     }
     if (pos >= 0) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) acc[c] += fJ[3 * (b + pos) + c];
+      for (int c = 0; c < 3; ++c) {
+        double t = fJ[3 * (b + pos) + c];
+        for (int v = 1; v < parts; ++v) t += fJ[v * fstride + 3 * (b + pos) + c];
+        acc[c] += t;
+      }
     }
   }
 #pragma unroll
@@ -813,8 +823,9 @@ __global__ void gather_forces_kernel(const int64_t* clus_ptr, const int32_t* clu
 // ---------------------------------------------------------------------------
 // launchers
 template <int NU, int R, int T>
-static const void* afn() {
-  return reinterpret_cast<const void*>(&adjoint_kernel<NU, R, T>);
+static const void* afn(bool split) {
+  return split ? reinterpret_cast<const void*>(&adjoint_kernel<NU, R, T, true>)
+               : reinterpret_cast<const void*>(&adjoint_kernel<NU, R, T, false>);
 }
 
 struct AdjShape {
@@ -822,11 +833,11 @@ struct AdjShape {
 };
 static const AdjShape kAdj[] = {{12, 768, 1}, {20, 768, 1}, {30, 768, 1}};
 
-static const void* adj_fn(int cap) {
+static const void* adj_fn(int cap, bool split = false) {
   switch (cap) {
-    case 12: return afn<12, 1, 768>();
-    case 20: return afn<20, 1, 768>();
-    case 30: return afn<30, 1, 768>();
+    case 12: return afn<12, 1, 768>(split);
+    case 20: return afn<20, 1, 768>(split);
+    case 30: return afn<30, 1, 768>(split);
     default: return nullptr;
   }
 }
@@ -857,7 +868,9 @@ int adjoint_occupancy(int cap) {
   static bool set[64] = {};
   if (!set[cap]) {
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) !=
-        hipSuccess) {
+            hipSuccess ||
+        hipFuncSetAttribute(adj_fn(cap, true), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)dyn) != hipSuccess) {
       (void)hipGetLastError();
       return 0;
     }
@@ -874,7 +887,7 @@ int adjoint_occupancy(int cap) {
 }
 
 hipError_t launch_adjoint(const AdjointArgs& a, int grid, hipStream_t s) {
-  const void* fn = adj_fn(a.cap);
+  const void* fn = adj_fn(a.cap, a.split != 0);
   if (!fn || grid <= 0) return hipErrorInvalidValue;
   int tpb = 0;
   for (const AdjShape& sh : kAdj)
@@ -908,10 +921,11 @@ hipError_t launch_adj_prep(const double* cvec, const double* cdg, const int32_t*
 }
 
 hipError_t launch_gather_forces(const int64_t* clus_ptr, const int32_t* clus_atoms, int64_t n,
-                                const double* fJ, double* F, hipStream_t s) {
+                                const double* fJ, int parts, int64_t fstride, double* F,
+                                hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(gather_forces_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s,
-                     clus_ptr, clus_atoms, n, fJ, F);
+                     clus_ptr, clus_atoms, n, fJ, parts, fstride, F);
   return hipGetLastError();
 }
 

@@ -408,6 +408,14 @@ static void record_plans(mag_ctx* ctx, const std::vector<KrylovShapeInfo>& shape
   }
 }
 
+// the exact gradient takes the columns of an atom one by one while the system
+// has at most four atoms per CU (61 atoms, nu = 12: 0.49 ms by atoms, 0.14 by
+// columns); of larger ones a workgroup takes whole atoms, which share the
+// cluster's tables
+static bool adjoint_split(const mag_ctx* ctx) {
+  return ctx->N <= 4 * (int64_t)device_count_cus(ctx->device);
+}
+
 // the exact gradient of one chunk of whole atoms whose pass-1 data (Ritz
 // vectors, basis, h, beta, last residual) are in the adj_* buffers: the
 // pencil's adjoint, the reverse sweep with the contraction, per-atom parts
@@ -417,7 +425,8 @@ static int adjoint_tail(mag_ctx* ctx, const ColumnJob& job, const int32_t* cols,
                          ctx->state.as<MuState>(), ctx->adj_hbar.as<double>(), ctx->stream));
   const int occ = std::max(1, adjoint_occupancy(cap));
   const int64_t natoms = cnt / NORB;
-  const int grid = (int)std::min<int64_t>(natoms, (int64_t)ncu * occ);
+  const bool split = adjoint_split(ctx);
+  const int grid = (int)std::min<int64_t>(split ? NORB * natoms : natoms, (int64_t)ncu * occ);
   ALLOC(ctx->adj_wbar, adjoint_scratch_per_wg(cap) * (size_t)grid);
   ALLOC(ctx->adj_counter, sizeof(int32_t));
   HIPCHK(launch_fill_i32(ctx->adj_counter.as<int32_t>(), 1, 0, ctx->stream));
@@ -438,6 +447,8 @@ static int adjoint_tail(mag_ctx* ctx, const ColumnJob& job, const int32_t* cols,
   aa.nu_eff = nu_eff;
   aa.wbar = ctx->adj_wbar.as<double>();
   aa.fJ = ctx->adj_fJ.as<double>();
+  aa.split = split ? 1 : 0;
+  aa.fstride = 3 * ctx->clus_total;
   aa.counter = ctx->adj_counter.as<int32_t>();
   aa.err = ctx->errflag.as<int32_t>();
   aa.cap = cap;
@@ -1954,7 +1965,8 @@ int mag_forces_exact(mag_ctx* ctx, const mag_sk_model* model, double* F, int mem
   if (adjoint_occupancy(cap) < 1)
     return fail(ctx, MAG_EUNSUPPORTED, "the exact-gradient kernel does not fit on this device");
   TRY(span_mark(ctx, SPAN_EXACT, 0));
-  ALLOC(ctx->adj_fJ, sizeof(double) * 3 * std::max<int64_t>(ctx->clus_total, 1));
+  const int parts = adjoint_split(ctx) ? NORB : 1;
+  ALLOC(ctx->adj_fJ, sizeof(double) * 3 * parts * std::max<int64_t>(ctx->clus_total, 1));
   ALLOC(ctx->adj_F, sizeof(double) * 3 * ctx->N);
   ColumnJob job;
   job.cols_dev = ctx->k_cols.as<int32_t>();
@@ -1987,7 +1999,8 @@ int mag_forces_exact(mag_ctx* ctx, const mag_sk_model* model, double* F, int mem
   ctx->stats.krylov_tpb = keep.krylov_tpb;
   ctx->stats.krylov_cache_blocks = keep.krylov_cache_blocks;
   HIPCHK(launch_gather_forces(ctx->clus_ptr.as<int64_t>(), ctx->clus_atoms.as<int32_t>(), ctx->N,
-                              ctx->adj_fJ.as<double>(), ctx->adj_F.as<double>(), ctx->stream));
+                              ctx->adj_fJ.as<double>(), parts, 3 * ctx->clus_total,
+                              ctx->adj_F.as<double>(), ctx->stream));
   TRY(copy_out(ctx, F, ctx->adj_F.p, sizeof(double) * 3 * ctx->N, mem_kind));
   TRY(span_mark(ctx, SPAN_EXACT, 1));
   TRY(flags_enqueue(ctx, FLAGS_CALL));

@@ -261,7 +261,9 @@ struct AdjointArgs {
   const int32_t* nu_eff;   // per slot, from the first pass over the chunk
   double* wbar;            // per workgroup: nu x (rows) scratch
   double* fJ;              // per atom J: its parts for its cluster atoms, at 3 clus_ptr[J]
-  int32_t* counter;        // atom counter of the persistent workgroups
+  int split;               // 1: a workgroup takes one column, and column alpha's parts
+  int64_t fstride;         //    start at fJ + alpha * fstride
+  int32_t* counter;        // counter of the persistent workgroups
   int32_t* err;
   int cap;
   // the forward pass's basis, last residual, h and beta per slot (layouts as
@@ -280,7 +282,8 @@ hipError_t launch_adjoint(const AdjointArgs& a, int grid, hipStream_t s);
 hipError_t launch_adj_prep(const double* cvec, const double* cdg, const int32_t* nu_eff,
                            int64_t ncols, int cap, const MuState* st, double* hbar, hipStream_t s);
 hipError_t launch_gather_forces(const int64_t* clus_ptr, const int32_t* clus_atoms, int64_t n,
-                                const double* fJ, double* F, hipStream_t s);
+                                const double* fJ, int parts, int64_t fstride, double* F,
+                                hipStream_t s);
 
 
 hipError_t launch_sk_count(const double* pos, int64_t n, const double cell[3], double rc,
