@@ -286,7 +286,7 @@ class Context:
                                                 n, C.c_void_p(zz.ctypes.data), nz,
                                                 C.c_void_p(out.ctypes.data),
                                                 C.c_void_p(off.ctypes.data), L.MAG_HOST))
-        return out[0::2] + 1j * out[1::2], off
+        return out.view(np.complex128), off
 
     def cocg_columns(self, cols, z, tol=1e-10, max_iter=2000):
         """Columns of (z S_C - H_C)^-1 by COCG on each column's cluster (see
@@ -308,7 +308,7 @@ class Context:
                                                int(max_iter), C.c_void_p(out.ctypes.data),
                                                C.c_void_p(off.ctypes.data),
                                                C.c_void_p(iters.ctypes.data), L.MAG_HOST))
-        return out[0::2] + 1j * out[1::2], off, iters
+        return out.view(np.complex128), off, iters
 
     def backward(self, gA=1.0):
         outs, ptrs, kind = self._outputs([((self.nnz,), np.float64), ((self.nnz,), np.float64)])
