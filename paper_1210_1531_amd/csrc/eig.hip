@@ -20,8 +20,8 @@
 //     straight-line code under a lane predicate.
 //  3. vectors (one wave per column): Z_T is rebuilt by replaying the recorded
 //     rotations on Z = I (lane i holds row i of Z; every register index is a
-//     compile-time constant; the rotations come through scalar loads, eight
-//     planes at a time, with the identity in planes outside the sweep), then
+//     compile-time constant; the rotations come through LDS, a sweep at a
+//     time, with the identity in planes outside the sweep), then
 //     c = L^-T Q_H Z_T column by column (lane k holds eigenvector k), so
 //     h c = eps s c and c^T s c = I.  Then
 //       d = c^T u = (Qc)^T e_l,  g = c^T s e_1 = (Qc)^T S_C e_l  (q_1 = e_l),
@@ -50,6 +50,7 @@ constexpr int ETPB = 64;
 // columns: 2.0 against 1.2 ms).  The two meet at 4,096 columns at every nu
 // from 12 to 48; the bits are the same.
 constexpr int64_t QL_WAVE_COLS = 4096;
+constexpr int VEC_AHEAD = 4;  // sweeps whose records are in flight
 constexpr int QL_MAXIT = 60;  // QL iterations per eigenvalue before giving up
 
 // rotation records: sweep q, plane i at q * eig_sweep_stride + i (planes padded to a
@@ -455,12 +456,11 @@ __device__ __forceinline__ bool ql_wave(const double* tr, int n, double* Z, doub
 // ---------------------------------------------------------------------------
 // 3. eigenvectors, spectral weights and pattern rows.  One wave per column,
 // lane k carries eigenvector k.  What this kernel reads of the column and
-// every lane needs (rotation record, reflectors, L) was written by earlier
+// every lane needs (reflectors, L) was written by earlier
 // kernels, so it is read through the constant address space: scalar loads
 // into SGPRs that feed the FMAs directly.  The pattern rows of Q, one per
 // lane, come by vector loads.
 typedef const __attribute__((address_space(4))) double kdouble;
-typedef const __attribute__((address_space(4))) int32_t kint;
 
 // WQL: the QL runs here too, inside the wave
 template <int NM, bool WQL>
@@ -493,37 +493,49 @@ __device__ __forceinline__ void vectors_column(const EigArgs& a, int64_t slot, d
     double z[NM];
 #pragma unroll
     for (int t = 0; t < NM; ++t) z[t] = (t == lane) ? 1.0 : 0.0;
+    // A sweep's record is one 16-byte read per lane (lane i: plane i), on its way
+    // VEC_AHEAD sweeps before it is used, because the records come from far
+    // (30 KB per column at nu = 30); LDS hands every lane the rotation of each
+    // plane, the identity in the planes outside the sweep
     const int nsw = a.qlst[slot];
     constexpr int SWS = eig_sweep_stride(NM);
-    kdouble* rec = (kdouble*)(a.rot + slot * (int64_t)(2 * a.rec_cap));  // (sn, cs) pairs
-    kint* sw = (kint*)(a.sweep + slot * (int64_t)a.sweep_cap);
-    // sweep (ms, cnt) rotated the planes i = ms-1 down to ms-cnt, in that order;
-    // its record is read eight planes at a time (two 64-byte scalar loads)
-    int hdr_next = nsw > 0 ? sw[0] : 0;
-    for (int q = 0; q < nsw; ++q) {
-      const int hdr = hdr_next;
-      if (q + 1 < nsw) hdr_next = sw[q + 1];  // in flight with the first group's loads
-      const int ms = hdr >> 8;
-      const int lo = ms - (hdr & 255);
-      kdouble* rq = rec + 2 * (int64_t)q * SWS;
+    const double2* rec = reinterpret_cast<const double2*>(a.rot) + slot * (int64_t)a.rec_cap +
+                         min(lane, SWS - 1);
+    const int32_t* sw = a.sweep + slot * (int64_t)a.sweep_cap;
+    const int hd0 = lane < nsw ? sw[lane] : 0, hd1 = 64 + lane < nsw ? sw[64 + lane] : 0;
+    double2* buf = reinterpret_cast<double2*>(sm);
+    double2 ring[VEC_AHEAD];
 #pragma unroll
-      for (int c = SWS / 8 - 1; c >= 0; --c) {
-        if (8 * c < ms && 8 * c + 8 > lo) {
-          double rr[16];
+    for (int u = 0; u < VEC_AHEAD; ++u)
+      if (u < nsw) ring[u] = rec[u * SWS];
+    for (int q0 = 0; q0 < nsw; q0 += VEC_AHEAD) {
 #pragma unroll
-          for (int u = 0; u < 16; ++u) rr[u] = rq[16 * c + u];
+      for (int u = 0; u < VEC_AHEAD; ++u) {
+        const int q = q0 + u;
+        if (q < nsw) {
+          // sweep (ms, cnt) rotated the planes i = ms-1 down to ms-cnt, in that order
+          const int hdr = __builtin_amdgcn_readlane(q < 64 ? hd0 : hd1, q & 63);
+          const int ms = hdr >> 8;
+          const int lo = ms - (hdr & 255);
+          if (lane < SWS)
+            buf[lane] = (lane < ms && lane >= lo) ? ring[u] : make_double2(0.0, 1.0);
+          if (q + VEC_AHEAD < nsw) ring[u] = rec[(q + VEC_AHEAD) * SWS];
+          __syncthreads();  // (one wave: only the order of its LDS accesses)
 #pragma unroll
-          for (int u = 7; u >= 0; --u) {
-            const int i = 8 * c + u;
-            if (i > NM - 2) continue;
-            // planes outside the sweep take the identity rotation (a scalar
-            // select): no per-lane predication
-            const bool on = i < ms && i >= lo;
-            const double sn = on ? rr[2 * u] : 0.0, cs = on ? rr[2 * u + 1] : 1.0;
-            const double zf = z[i + 1];
-            z[i + 1] = fma(sn, z[i], cs * zf);
-            z[i] = fma(cs, z[i], -sn * zf);
+          for (int c = SWS / 8 - 1; c >= 0; --c) {
+            if (8 * c < ms && 8 * c + 8 > lo) {
+#pragma unroll
+              for (int v = 7; v >= 0; --v) {
+                const int i = 8 * c + v;
+                if (i > NM - 2) continue;
+                const double2 r = buf[i];
+                const double zf = z[i + 1];
+                z[i + 1] = fma(r.x, z[i], r.y * zf);
+                z[i] = fma(r.y, z[i], -r.x * zf);
+              }
+            }
           }
+          __syncthreads();
         }
       }
     }
