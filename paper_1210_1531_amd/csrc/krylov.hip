@@ -1116,8 +1116,10 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
 // Workgroup shapes: eight waves, two columns of an atom in up to 768 rows for
 // nu <= 30 (half of the basis vectors of RPL rows in a lane: nu = 30 takes 60,
 // 120, 150 or 180 registers for clusters of up to 64, 128, 160 or 192 atoms).
-// At nu = 40 and 48 two columns fit up to 128 atoms; a larger cluster takes the
-// whole workgroup for one column.  A column's shape follows from nu and its
+// Two columns take 200 registers at nu = 40 and 160 atoms, 192 at nu = 48 and 128:
+// some of the rest then lives in scratch, which still costs less than a
+// workgroup for one column (3,892 atoms, r = 6, nu = 40: 15.9 against 17.3 ms).
+// Beyond that a cluster takes the whole workgroup for one column.  A column's shape follows from nu and its
 // cluster's size alone: a smaller shape has fewer instructions per step and
 // holds more of H in LDS, so the smallest that holds a cluster is the fastest
 // one (160-atom clusters at nu = 30: 7.5 ms with 5 rows against 9.9 ms with 6).
@@ -1128,7 +1130,7 @@ static constexpr ShapeDef kShapes[] = {
     {12, 2, 2}, {12, 2, 4}, {12, 2, 6},
     {20, 2, 2}, {20, 2, 4}, {20, 2, 5}, {20, 2, 6},
     {30, 2, 2}, {30, 2, 4}, {30, 2, 5}, {30, 2, 6},
-    {40, 2, 2}, {40, 2, 4}, {40, 1, 3},
+    {40, 2, 2}, {40, 2, 4}, {40, 2, 5}, {40, 1, 3},
     {48, 2, 2}, {48, 2, 4}, {48, 1, 3},
 };
 constexpr int kNumShapes = (int)(sizeof(kShapes) / sizeof(kShapes[0]));
