@@ -74,8 +74,11 @@ constexpr int PAIR_CACHE = 1024;           // LDS bytes of one cached pair of ti
 // offsets of its two column atoms' operands (16 bits each), and the places of
 // the two blocks in the global array, in units of 16 bytes
 constexpr int TAB_UNIT = 96, TAB_B = 32;   // bytes of both, offset of the second
-// streamed units read ahead: eight registers each, next to the basis
-constexpr int stream_ring(int nu, int rpl) { return nu * rpl > 140 ? 2 : 4; }
+// streamed units read ahead, eight registers each next to the basis (an even
+// number, as the operands alternate between two places): with four instead of
+// two the smaller shapes gain nothing and the larger spill (3,892 atoms, nu = 30:
+// r = 5, 120 registers of basis, 5.36 against 5.04 ms; r = 6, 150, 10.6 against 7.3)
+constexpr int RING = 2;
 constexpr int PAD_UNITS = 2;               // dummy units after a wave's last
 
 // LDS bytes of an operand buffer and of the product
@@ -268,7 +271,6 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
   constexpr int PA = proj_atom(ROWS, NCOL);   // bytes of an atom's vectors
   constexpr int PQ = NCOL * CB * 16;    // ... of one orbital pair
   constexpr int TPW = tiles_per_wave(ROWS);
-  constexpr int RING = stream_ring(NU, RPL);
   static_assert(NU % 2 == 0, "even and odd vectors");
   static_assert(pool_bytes(ROWS, NCOL, NSET) + LDS_STATIC <= LDS_CU, "LDS of a CU");
   __shared__ int32_t s_atoms[CLUSTER_MAX];
