@@ -40,9 +40,9 @@
 // (a third of it from the cache), local subtraction 1,500, dots 1,300, totals,
 // subtraction and store 4,100; the projection adds about 5,000 per step.
 // Measured (MI355X, nu = 30, all 15,568 columns of 3,892 atoms in one launch):
-// 7.5 ms; one column per 768-thread workgroup with vector FMA and two full
+// 7.3 ms; one column per 768-thread workgroup with vector FMA and two full
 // orthogonalization passes took 13.5 ms.  The 29,000-atom void cell at nu =
-// 20, clusters up to 164 atoms: 33 against 61 ms; nu = 48 at 3,892 atoms and
+// 20, clusters up to 164 atoms: 32 against 61 ms; nu = 48 at 3,892 atoms and
 // r = 4.5: 13 against 23 ms.
 //
 // Scheduling: persistent workgroups pull columns from KRYLOV_QUEUES device
@@ -1124,7 +1124,7 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
 // Beyond that a cluster takes the whole workgroup for one column.  A column's shape follows from nu and its
 // cluster's size alone: a smaller shape has fewer instructions per step and
 // holds more of H in LDS, so the smallest that holds a cluster is the fastest
-// one (160-atom clusters at nu = 30: 7.5 ms with 5 rows against 9.9 ms with 6).
+// one (160-atom clusters at nu = 30: 7.3 ms with 5 rows against 9.9 ms with 6).
 struct ShapeDef {
   int cap, ncol, rpl;
 };
