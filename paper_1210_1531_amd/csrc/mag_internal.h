@@ -78,6 +78,7 @@ struct MuState {
   int guess;        // the next round's points are pts (else the interval tree)
   int tree;         // no further guesses
   double pts[32];
+  double ylo, yhi;  // N - N_e at lo and hi (ylo >= 0, yhi < 0: not evaluated yet)
 };
 
 struct KrylovArgs {

@@ -10,14 +10,15 @@
 // with the plain rule; the result is the same sequence of brackets as plain
 // bisection, five levels per launch.  Once the bracket is narrow on the kT
 // scale N(mu) is smooth inside it: the root is guessed by inverse cubic
-// interpolation of the points evaluated last and the next 31 points are placed
-// about the guess, in geometric distances.  N is monotone, so the points next
-// to the root decide every midpoint outside them, and plain bisection's
-// sequence goes on until a midpoint falls between the two: the last 40 or so
-// halvings take three launches or four instead of eight.  A guess that decides fewer than five levels is the
-// last one.  Reductions are deterministic: fixed
-// grid-stride partition, fixed in-block order, and the last block to finish
-// sums the per-block partials in block order.
+// interpolation of the points next to it, and the next 31 points are the
+// midpoints that plain bisection would take if the guess were the root.  The
+// walk goes on as long as N at each of them sends it to the next one, so every
+// halving is still decided by N at its own midpoint (N need not be monotone:
+// some weights are negative) and only the number of launches depends on the
+// guess: the last 40 or so halvings take two launches or three instead of
+// eight.  A guess that decides fewer than five levels is the last one.
+// Reductions are deterministic: fixed grid-stride partition, fixed in-block
+// order, and the last block to finish sums the per-block partials in block order.
 #include "mag_internal.h"
 #include "wave.h"
 
@@ -279,96 +280,69 @@ __global__ __launch_bounds__(MTPB) void mu_round_kernel(const double* eps, const
     __syncthreads();
     if (tid >= 64) return;
     // (every lane of the first wave does the same, lane 0 writes)
-    double lo = lo0, hi = hi0;
-    int lev = st->levels, done = 0;
+    double lo = lo0, hi = hi0, ylo = st->ylo, yhi = st->yhi;
+    int lev = st->levels, n = 1;
     const double ne = st->ne, tol = st->tol;
-    // the points next to the root: N < N_e up to a1, N >= N_e from b1 on
-    double a1 = lo, b1 = hi, a2 = lo, b2 = hi, ya1 = 0.0, yb1 = 0.0, ya2 = 0.0, yb2 = 0.0;
-    bool ha1 = false, hb1 = false, ha2 = false, hb2 = false;  // evaluated, not the bracket's end
-#pragma unroll
-    for (int p = 0; p < MPTS; ++p) {
-      const double x = s_pts[p];
-      if (s_N[p] >= ne && x < b1) b1 = x;
-    }
-#pragma unroll
-    for (int p = 0; p < MPTS; ++p) {
-      const double x = s_pts[p];
-      if (s_N[p] < ne && x < b1 && x > a1) a1 = x;
-    }
-    if (guess) {
-      // (bounded: a tolerance below the spacing of doubles never ends it)
-      for (int l = 0; l < 64 && hi - lo > tol; ++l) {
-        const double mid = lo + (hi - lo) / 2.0;
-        if (mid <= a1) lo = mid;
-        else if (mid >= b1) hi = mid;
-        else break;
-        ++lev;
+    for (int l = 0; l < (guess ? MPTS : MLEV) && hi - lo > tol; ++l) {
+      const double mid = lo + (hi - lo) / 2.0;
+      if (guess && s_pts[l] != mid) break;  // the guess was on the other side
+      const double y = s_N[guess ? l : n - 1] - ne;
+      if (y < 0.0) {
+        lo = mid;
+        ylo = y;
+        n = 2 * n + 1;
+      } else {
+        hi = mid;
+        yhi = y;
+        n = 2 * n;
       }
-    } else {
-      int n = 1;
-      for (int l = 0; l < MLEV; ++l) {
-        if (!(hi - lo > tol)) {
-          done = 1;
-          break;
-        }
-        const double mid = lo + (hi - lo) / 2.0;
-        if (s_N[n - 1] < ne) {
-          lo = mid;
-          n = 2 * n + 1;
-        } else {
-          hi = mid;
-          n = 2 * n;
-        }
-        ++lev;
-      }
+      ++lev;
     }
-    if (!(hi - lo > tol)) done = 1;
-    // the next round's points: the tree, or points about a guess of the root,
+    const bool done = !(hi - lo > tol);
+    // the next round's points: the tree, or the way to a guess of the root,
     // unless guesses have brought less than a tree before
     const bool tree = st->tree != 0 || (guess && lev < st->levels + MLEV);
-    const bool next = !done && !tree && hi - lo <= 2.0 * kT;
-    if (next) {
+    bool next = false;
+    if (!done && !tree && hi - lo <= 2.0 * kT && ylo < 0.0 && yhi >= 0.0) {
+      // the nearest points outside the bracket (its former ends among them)
+      double a2 = 0.0, b2 = 0.0, ya2 = 0.0, yb2 = 0.0;
+      bool ha = false, hb = false;
+      auto take = [&](double x, double y) {
+        if (x < lo && (!ha || x > a2)) a2 = x, ya2 = y, ha = true;
+        if (x > hi && (!hb || x < b2)) b2 = x, yb2 = y, hb = true;
+      };
 #pragma unroll
-      for (int p = 0; p < MPTS; ++p) {
-        const double x = s_pts[p], y = s_N[p] - ne;
-        if (x == a1) ya1 = y, ha1 = true;
-        if (x == b1) yb1 = y, hb1 = true;
-        if (x < a1 && (!ha2 || x > a2)) a2 = x, ya2 = y, ha2 = true;
-        if (x > b1 && (!hb2 || x < b2)) b2 = x, yb2 = y, hb2 = true;
-      }
-      double g = a1 + (b1 - a1) / 2.0, err = b1 - a1;
-      if (ha1 && hb1 && ha2 && hb2 && ya2 < ya1 && ya1 < yb1 && yb1 < yb2) {
+      for (int p = 0; p < MPTS; ++p) take(s_pts[p], s_N[p] - ne);
+      if (st->ylo < 0.0) take(lo0, st->ylo);
+      if (st->yhi >= 0.0) take(hi0, st->yhi);
+      if (ha && hb && ya2 < ylo && yhi < yb2) {
         // N(mu) interpolated inversely: the line through the two, Neville's
         // cubic through all four, both at N_e
-        const double l0 = a1 - ya1 * ((b1 - a1) / (yb1 - ya1));
-        const double m0 = a2 - ya2 * ((a1 - a2) / (ya1 - ya2));
-        const double m2 = b1 - yb1 * ((b2 - b1) / (yb2 - yb1));
-        const double q0 = (yb1 * m0 - ya2 * l0) / (yb1 - ya2);
-        const double q1 = (yb2 * l0 - ya1 * m2) / (yb2 - ya1);
+        const double l0 = lo - ylo * ((hi - lo) / (yhi - ylo));
+        const double m0 = a2 - ya2 * ((lo - a2) / (ylo - ya2));
+        const double m2 = hi - yhi * ((b2 - hi) / (yb2 - yhi));
+        const double q0 = (yhi * m0 - ya2 * l0) / (yhi - ya2);
+        const double q1 = (yb2 * l0 - ylo * m2) / (yb2 - ylo);
         const double c0 = (yb2 * q0 - ya2 * q1) / (yb2 - ya2);
-        if (c0 > a1 && c0 < b1) {
-          g = c0;
-          err = fabs(c0 - l0);
+        const double g = (c0 > lo && c0 < hi) ? c0 : l0;
+        next = true;
+        double a = lo, b = hi;
+        for (int l = 0; l < MPTS; ++l) {
+          const double mid = a + (b - a) / 2.0;
+          if (tid == l) st->pts[l] = mid;
+          if (mid < g) a = mid;
+          else b = mid;
         }
-      }
-      // fifteen points on each side of the guess at distances from smin to the
-      // known bracket's width, a constant ratio apart, and plain bisection's
-      // next midpoint
-      const double smax = b1 - a1;
-      const double smin = fmax(fmax(tol / 64.0, 1e-5 * err), 1e-15 * fabs(g));
-      const double lr = log2(fmax(smax / smin, 1.0)) * (1.0 / 14.0);
-      if (tid < MPTS) {
-        const double sd = smin * exp2(lr * (double)(tid >> 1));
-        const double mid = lo + (hi - lo) / 2.0;
-        st->pts[tid] = tid == MPTS - 1 ? mid : ((tid & 1) ? g + sd : g - sd);
       }
     }
     if (tid == 0) {
       st->lo = lo;
       st->hi = hi;
       st->levels = lev;
-      st->done = done;
+      st->done = done ? 1 : 0;
       st->mu = lo + (hi - lo) / 2.0;
+      st->ylo = ylo;
+      st->yhi = yhi;
       st->guess = next ? 1 : 0;
       st->tree = tree ? 1 : 0;
       st->counter = 0;
@@ -422,6 +396,7 @@ __global__ void mu_setup_kernel(MuState* st, double ne, double kT, double tol, d
   h.ne = ne;
   h.kT = kT;
   h.tol = tol;
+  h.yhi = -1.0;
   if (fixed) {
     h.mu = mu_fixed;
     h.done = 1;
