@@ -14,7 +14,7 @@
 // The local subtraction removes what cancels most (H is symmetric, so h is
 // tridiagonal up to rounding), so the one full pass leaves w orthogonal to a
 // few ulps; when it still removes more than half of |w|^2 (an almost invariant
-// space) a second pass runs, with the norm taken explicitly.  The basis is
+// space) two more passes run, and the last one's |w|^2 - |c|^2 is the norm.  The basis is
 // Euclidean-orthonormal; it spans the same Krylov space K_nu(H_C; e_l) as the
 // S-orthonormal basis of the method's reading, so the projected pencil (h, s)
 // has the same Ritz pairs.
@@ -226,7 +226,10 @@ __device__ __forceinline__ void put3(double& a0, double& a1, double& a2, double&
 // a value that is the same in every lane, in a scalar register: conditions on
 // it become scalar branches.  (They have to: where a lane-masked region ends
 // together with one that encloses it, the compiler has been seen to reload a
-// spilled basis register under the inner mask.)
+// spilled basis register under the inner mask.)  Scalar branches around the
+// places where a vector enters the basis make it spill the basis instead (nu =
+// 30, 160 atoms: 195 registers against 35), so there what a column does follows
+// from selects.
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int64_t uni(int64_t v) {
   return ((int64_t)uni((int)(v >> 32)) << 32) | (uint32_t)uni((int)v);
@@ -715,9 +718,11 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
         csq = row_allreduce(csq);
         return swap16_add(csq, csq);
       };
-      // q_cn = w into its register column (put_column) and the operand buffer xb
-      auto store_q = [&](const double(&w)[RPL], int cn, char* xb) __attribute__((always_inline)) {
-        const int tn = __builtin_amdgcn_readfirstlane(cn >> 1);
+      // q_cn = w into its register column (none of them unless put) and, in the
+      // lanes of `own_x`, the operand buffer xb
+      auto store_q = [&](const double(&w)[RPL], int cn, bool put, bool own_x,
+                         char* xb) __attribute__((always_inline)) {
+        const int tn = __builtin_amdgcn_readfirstlane(put ? cn >> 1 : NU);
         const uint64_t own = (cn & 1) ? 0xffff0000ffff0000ull : 0x0000ffff0000ffffull;
         static_for<0, (NB + 1) / 2>([&](auto ti) __attribute__((always_inline)) {
           constexpr int T = decltype(ti)::value, t0 = 2 * T;
@@ -739,7 +744,7 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
             put2<T>(qv[n3 + 4][t0], qv[n3 + 5][t0], odd(n3 + 4), odd(n3 + 5), w[n3 + 4],
                     w[n3 + 5], tn, own);
         });
-        if (g == 0) {
+        if (own_x) {
           const int pr = opaque(p0);
           char* xo = xb + ((pr >> 1) & 1) * PL + (pr >> 2) * 32 + (NCOL == 2 ? col : 0) * 16 +
                      (pr & 1) * 8;
@@ -748,8 +753,8 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
         }
       };
       // the residual of a column's last step for the exact gradient
-      auto store_last = [&](const double(&w)[RPL]) __attribute__((always_inline)) {
-        if (g == 0) {
+      auto store_last = [&](const double(&w)[RPL], bool last) __attribute__((always_inline)) {
+        if (g == 0 && last) {
 #pragma unroll
           for (int m = 0; m < RPL; ++m) {
             const int r = p0 + LROWS * m;
@@ -759,15 +764,19 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
         }
       };
 
-      // the next basis vector from the orthogonalized w
-      auto advance = [&](double(&w)[RPL], double b2, int k) __attribute__((always_inline)) {
-        const double inv = rsqrt(b2);
-        beta_prev = b2 * inv;
-        if (ADJ && wv == 0 && lane == 0) a.adj_beta[slot * (int64_t)cap + k] = beta_prev;
+      // the next basis vector from the orthogonalized w, if the column goes on
+      auto advance = [&](double(&w)[RPL], double b2, int k, bool go, bool own_x)
+          __attribute__((always_inline)) {
+        const double inv = go ? rsqrt(b2) : 1.0;
+        beta_prev = go ? b2 * inv : beta_prev;
+        if (ADJ && go && wv == 0 && lane == 0) a.adj_beta[slot * (int64_t)cap + k] = beta_prev;
 #pragma unroll
         for (int m = 0; m < RPL; ++m) w[m] *= inv;
-        store_q(w, k + 1, s_x + ((k & 1) ^ 1) * XB);
+        store_q(w, k + 1, go, own_x, s_x + ((k & 1) ^ 1) * XB);
       };
+      // a condition that all lanes share, as a scalar up to nu = 30; beyond that it
+      // stays in the lanes (forces of 3,600 atoms at nu = 40: 16.4 against 16.9 ms)
+      auto any = [](bool c) { return NU > 30 ? c : __builtin_amdgcn_ballot_w64(c) != 0; };
       bool more = true;
       for (int k = 0; k < nu_max && more; ++k) {
         char* xb = s_x + (k & 1) * XB;
@@ -919,48 +928,41 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
           beta2 = norm - subtract(w, hv, k);
           const bool finite = isfinite(ww1);
           if (!finite && wv == 0 && lane == 0) atomicOr(a.err, (int)KERR_NONFINITE);
-          if (!finite || k + 1 >= nu_max) st = ST_DONE;
-          else if (!(beta2 > 0.5 * norm)) st = ST_AGAIN;
-          else st = (beta2 > a.breakdown * a.breakdown * ww1) ? ST_GO : ST_DONE;
-          if (st == ST_GO) {
-            advance(w, beta2, k);
-          } else if (st == ST_DONE) {
-            nu_eff = k + 1;
-            if (ADJ) store_last(w);
-          }
+          const bool half = !(beta2 > 0.5 * norm);
+          const bool small = !(beta2 > a.breakdown * a.breakdown * ww1);
+          st = any(!finite) || k + 1 >= nu_max
+                   ? (int)ST_DONE
+                   : (any(half) ? (int)ST_AGAIN : (any(small) ? (int)ST_DONE : (int)ST_GO));
+          advance(w, beta2, k, st == ST_GO, g == 0 && st == ST_GO);
+          nu_eff = st == ST_DONE ? k + 1 : nu_eff;
+          if (ADJ) store_last(w, st == ST_DONE);
         }
         if (wv == 0 && lane == 0) s_ctl[NCOL == 2 ? col : 0] = st;
         __syncthreads();
         int c_0 = __builtin_amdgcn_readfirstlane(s_ctl[0]);
         int c_1 = NCOL == 2 ? __builtin_amdgcn_readfirstlane(s_ctl[1]) : (int)ST_DONE;
         if (__builtin_expect(c_0 == ST_AGAIN || c_1 == ST_AGAIN, 0)) {
-          // rare: almost invariant spaces
-          const bool again = st == ST_AGAIN;
+          // rare: almost invariant spaces.  The partner's w goes along, unused
+          const bool again = (NCOL == 2 && col == 1 ? c_1 : c_0) == ST_AGAIN;
           for (int pass = 0; pass < 2; ++pass) {
-            if (again) dots(w, k, red, std::true_type{});
+            dots(w, k, red, std::true_type{});
             __syncthreads();
-            if (again) {
-              totals(hv, k);
-              norm = lane_value(hv[0], k < 14 ? 7 : 15);
-              beta2 = norm - subtract(w, hv, k);
-            }
+            totals(hv, k);
+            norm = lane_value(hv[0], k < 14 ? 7 : 15);
+            beta2 = norm - subtract(w, hv, k);
             __syncthreads();
           }
-          if (again) {
-            st = (beta2 > a.breakdown * a.breakdown * ww1) ? ST_GO : ST_DONE;
-            if (st == ST_GO) {
-              advance(w, beta2, k);
-            } else {
-              nu_eff = k + 1;
-              if (ADJ) store_last(w);
-            }
-            if (wv == 0 && lane == 0) s_ctl[NCOL == 2 ? col : 0] = st;
-          }
+          const int go = any(beta2 > a.breakdown * a.breakdown * ww1) ? (int)ST_GO : (int)ST_DONE;
+          st = again ? go : st;
+          advance(w, beta2, k, again && st == ST_GO, again && g == 0);
+          nu_eff = again && st == ST_DONE ? k + 1 : nu_eff;
+          if (ADJ) store_last(w, again && st == ST_DONE);
+          if (wv == 0 && lane == 0) s_ctl[NCOL == 2 ? col : 0] = st;
           __syncthreads();
           c_0 = __builtin_amdgcn_readfirstlane(s_ctl[0]);
           c_1 = NCOL == 2 ? __builtin_amdgcn_readfirstlane(s_ctl[1]) : (int)ST_DONE;
         }
-        act = st == ST_GO;
+        act = (NCOL == 2 && col == 1 ? c_1 : c_0) == ST_GO;
         more = c_0 == ST_GO || c_1 == ST_GO;
       }
 
