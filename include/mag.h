@@ -89,7 +89,8 @@ enum mag_workflow {
  * which follows from nu and the cluster size.  PERSISTENT: per
  * bucket, one launch of resident workgroups pulling columns from eight
  * device queues of spatially contiguous columns (one per XCD, with
- * stealing).  GRID: per bucket, one launch with one workgroup per column.
+ * stealing).  GRID: per bucket, one launch with one workgroup per column (per
+ * two or four columns of an atom once there are more than the chip holds).
  * PLAIN: one launch per column.  GRAPH: PERSISTENT launches, with the whole
  * forward solve (Krylov passes, eigensolves, bisection for mu, energies)
  * captured once in a HIP graph and replayed by later solves with the same

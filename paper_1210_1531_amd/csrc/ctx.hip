@@ -595,6 +595,7 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
         KrylovArgs k1 = ka;
         k1.cols = ka.cols + q;
         k1.ncols = 1;
+        k1.group = 1;
         k1.hs = ka.hs + q * 2 * cap * cap;
         k1.urow = ka.urow + q * cap;
         k1.qpat = ka.qpat + q * (int64_t)pat_stride * cap;
@@ -703,13 +704,19 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
         kb.slots = dslots + boff[b];
         kb.ncols = nb;
         kb.cache_cap = pl.cache / KRYLOV_UNIT_BLOCKS;
+        const int64_t wgs = (int64_t)ncu * pl.per_cu;
+        // GRID: an atom's columns together or in pairs, as the queues hand them
+        // out, once there are more columns than workgroups the chip holds (solve of
+        // 3,892 atoms: nu = 12, r = 3: 1.9 against 3.1 ms by single columns, nu =
+        // 30, r = 6: 9.2 against 15.3)
+        kb.group = nb > 2 * NORB * wgs ? NORB : (nb > wgs ? 2 : 1);
         int grid = (int)nb;
         if (schedule == MAG_SCHED_PERSISTENT) {
           HIPCHK(launch_fill_i32(dqueue + KRYLOV_QUEUES * b, KRYLOV_QUEUES, 0, ctx->stream));
           kb.queue = dqueue + KRYLOV_QUEUES * b;
           kb.qbeg = dqbeg + (KRYLOV_QUEUES + 1) * b;
           kb.nqueue = KRYLOV_QUEUES;
-          grid = (int)std::min<int64_t>(nb, (int64_t)ncu * pl.per_cu);
+          grid = (int)std::min<int64_t>(nb, wgs);
         }
         HIPCHK(launch_krylov(kb, pl.shape, pl.dyn, grid, ctx->stream));
       }

@@ -344,8 +344,22 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
       if (base < 0) break;
     } else {
       if (it > 0) break;
-      base = blockIdx.x;
-      count = 1;
+      // the first workgroups take the first position of each group and those
+      // after it of the same atom, the others one of the rest, if it is still to
+      // be done
+      const int64_t ngr = (a.ncols + a.group - 1) / a.group;
+      const int64_t rest = (int64_t)blockIdx.x - ngr;
+      base = rest < 0 ? (int64_t)blockIdx.x * a.group
+                      : rest / (a.group - 1) * a.group + 1 + rest % (a.group - 1);
+      if (base >= a.ncols) break;
+      auto atom = [&](int64_t p) { return uni(a.cols[a.slots ? (int64_t)a.slots[p] : p]) >> 2; };
+      const int64_t first = base / a.group * a.group;
+      const int64_t last = min(first + a.group, a.ncols);
+      const int J0 = atom(first);
+      int64_t end = first + 1;
+      while (end < last && atom(end) == J0) ++end;
+      if (base != first && base < end) break;
+      count = base == first ? (int)(end - first) : 1;
     }
     if (base >= a.ncols) break;
 
@@ -1232,7 +1246,8 @@ int krylov_occupancy(int id, size_t dyn) {
 
 hipError_t launch_krylov(const KrylovArgs& a, int id, size_t dyn, int grid, hipStream_t s) {
   const void* fn = shape_fn(id, a.adj_q != nullptr);
-  if (!fn || grid <= 0 || dyn < krylov_pool_min(id)) return hipErrorInvalidValue;
+  if (!fn || grid <= 0 || dyn < krylov_pool_min(id) || (!a.queue && a.group < 1))
+    return hipErrorInvalidValue;
   KrylovArgs copy = a;
   copy.pool = (int)dyn;
   void* args[] = {&copy};

@@ -89,7 +89,8 @@ struct KrylovArgs {
   const int32_t* clus_atoms;
   const int32_t* cols;     // columns of this launch, in slot order
   int64_t ncols;
-  int32_t* queue;          // persistent: one counter per queue, or nullptr (one column per WG)
+  int32_t* queue;          // persistent: one counter per queue, or nullptr (no queues)
+  int group;               // not persistent: list positions dealt out together
   const int64_t* qbeg;     // persistent: slot range [qbeg[q], qbeg[q+1]) of queue q
   int nqueue;              // persistent: number of queues (workgroup w starts on queue w % nqueue)
   int nu;                  // requested Krylov dimension (<= template capacity)
