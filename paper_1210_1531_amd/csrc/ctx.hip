@@ -1418,12 +1418,18 @@ int mag_get_clusters(mag_ctx* ctx, int64_t* clus_ptr, int32_t* clus_atoms, int64
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-// bisection launches for brackets up to 1e7 eV wide at tolerance tol (five
-// levels per launch, but for one that a poor guess of the root may cost);
-// launches after convergence return at once
-static int mu_rounds(double tol) {
+// halvings granted: for brackets up to 1e7 eV wide at tolerance tol, in whole trees
+static int mu_levels(double tol) {
   const int levels = (int)std::ceil(std::log2(1e7 / tol)) + 2;
-  return (levels + mu_levels_per_round() - 1) / mu_levels_per_round() + 1;
+  return (levels + mu_levels_per_round() - 1) / mu_levels_per_round() * mu_levels_per_round();
+}
+
+// bisection launches for them (five levels per launch, but for one that a poor
+// guess of the root may cost); launches after convergence return at once
+static int mu_rounds(double tol) { return mu_levels(tol) / mu_levels_per_round() + 1; }
+
+static double mu_tolerance(const mag_opts* opts) {
+  return opts->mu_tol > 0 ? opts->mu_tol : 1e-12;
 }
 
 static int mu_grid(const mag_ctx* ctx) {
@@ -1445,7 +1451,7 @@ static int enqueue_mu(mag_ctx* ctx, const mag_opts* opts, bool fixed) {
   const int grid = mu_grid(ctx);
   ALLOC(ctx->partials, sizeof(double) * 64 * (size_t)grid);
   MuState* st = ctx->state.as<MuState>();
-  const double tol = opts->mu_tol > 0 ? opts->mu_tol : 1e-12;
+  const double tol = mu_tolerance(opts);
   HIPCHK(launch_mu_setup(st, opts->n_electrons, opts->kT, tol, opts->mu_fixed, fixed ? 1 : 0,
                          ctx->stream));
   if (!fixed) {
@@ -1467,7 +1473,9 @@ static int finish_solve(mag_ctx* ctx, const mag_opts* opts, bool fixed, double* 
                         double* E_band, double* A_free) {
   ctx->stats.bisect_levels = ctx->h_state.levels;
   if (ctx->h_state.err & KERR_NONFINITE) return fail(ctx, MAG_ENONFINITE, "non-finite Ritz data");
-  if (!fixed && !ctx->h_state.done)
+  // (a good guess may decide more than the granted halvings: a wider bracket is
+  // refused all the same)
+  if (!fixed && (!ctx->h_state.done || ctx->h_state.levels > mu_levels(mu_tolerance(opts))))
     return fail(ctx, MAG_EBRACKET, "bisection did not reach the tolerance");
   if (!std::isfinite(ctx->h_state.E) || !std::isfinite(ctx->h_state.mu))
     return fail(ctx, MAG_ENONFINITE, "non-finite energy");
