@@ -164,11 +164,11 @@ def krylov_roofline(ctx, s, st, t_launch_ms, launches_per_pass=1):
     model per launch (per column nu nnz_C 20 B / 4, the cluster's H, S values
     and index read once per Krylov step and shared by the atom's four columns,
     plus the pattern outputs 2 n_pat 8 B and the spectra 2 nu 8 B) over the
-    launch's duration, against HBM peak; the streamed blocks actually issued
-    per launch (for each pair of an atom's columns, every step re-reads the H
-    half, 128 B, of each non-cached block, and the projection the S half of
-    every block once per four basis vectors of each) against the vector-memory
-    ceiling; FP64 rate."""
+    launch's duration, against HBM peak; the least that the streamed blocks
+    issue per launch (for each pair of an atom's columns, every step re-reads
+    the H half, 128 B, of each block outside the LDS, which holds at most
+    cache_blocks, and the projection the S half of every block once per four
+    basis vectors of each) against the vector-memory ceiling; FP64 rate."""
     nu = s.nu
     M = 4 * s.n_atoms
     bytes_pass = 20.0 * nu * st["sum_cluster_nnz"] + 16.0 * ctx.nnz + 16.0 * nu * M
@@ -190,9 +190,9 @@ def krylov_roofline(ctx, s, st, t_launch_ms, launches_per_pass=1):
         "model": "streamed-cluster bytes: every Krylov step reads the cluster's H, S values "
                  "and indices once, shared by the atom's four columns; this working set is "
                  "served from LDS, L2 and MALL, not HBM, so the fraction can exceed 1",
-        "vmem": {"issued_bytes_per_launch": vmem, "achieved_GBs": vmem_gbs,
-                 "ceiling_GBs": VMEM_PEAK_GBS, "frac": vmem_gbs / VMEM_PEAK_GBS,
-                 "cache_blocks": int(st["krylov_cache_blocks"])},
+        "vmem": {"issued_bytes_per_launch_at_least": vmem, "GBs_at_least": vmem_gbs,
+                 "ceiling_GBs": VMEM_PEAK_GBS, "frac_at_least": vmem_gbs / VMEM_PEAK_GBS,
+                 "cache_blocks_at_most": int(st["krylov_cache_blocks"])},
     }
 
 
@@ -204,7 +204,7 @@ def launch_plans(st):
             continue
         out.append({"bucket": b, "threads": tpb, "rows_per_thread": st["plan_rows"][b],
                     "workgroups_per_cu": st["plan_per_cu"][b],
-                    "cached_blocks": st["plan_cache"][b],
+                    "cached_blocks_at_most": st["plan_cache"][b],
                     "candidates": st["plan_candidates"][b],
                     "columns": int(st["plan_columns"][b]),
                     "tuned_us_per_column": st["plan_us_per_col"][b]})

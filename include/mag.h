@@ -492,7 +492,8 @@ typedef struct {
   double t_md_step_ms;     /* last mag_md_run: average wall time of one step */
   double t_cocg_ms;        /* last mag_cocg_columns (its kernels) */
   double t_forces_exact_ms; /* last mag_forces_exact */
-  int32_t krylov_cache_blocks; /* H blocks of each cluster held in LDS by the largest bucket's plan */
+  int32_t krylov_cache_blocks; /* H blocks of a cluster held in LDS at most by the largest bucket's plan
+                                  (a cluster's own tables take part of the room) */
   /* the launch plan of each cluster-size bucket of the last pass 1 (bucket b
      holds the clusters between the row capacities of the shapes b-1 and b;
      entries of unused buckets are 0) */
