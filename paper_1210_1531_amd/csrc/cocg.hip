@@ -30,13 +30,13 @@ constexpr int CG_WAVES = CG_TPB / 64;
 // The blocks of a row that stay in registers over all iterations (one energy per
 // workgroup): as many as fit 168 registers, three waves on a SIMD
 constexpr int CG_KEPT = 3;
-// Up to this many (column, energy) pairs a workgroup takes one energy: the
+// Up to this many (column, energy) pairs per CU a workgroup takes one energy: the
 // chip has room for them all, and an iteration is shorter (64 columns of 4
 // energies on clusters of 156 atoms: 6.1 ms, four energies together 13.5 ms).
 // With more of them sharing the matrix reads counts (480 columns of 4: 28 ms
-// together); the two meet at about three pairs per CU (192 columns of 4:
-// 12.1 against 14.6 ms, 240: 15.2 against 14.9 ms).
-constexpr int64_t CG_SPLIT_WG = 768;
+// together); the two meet at about three pairs per CU (256 CUs, 192 columns of
+// 4: 12.1 against 14.6 ms, 240: 15.2 against 14.9 ms).
+constexpr int CG_SPLIT_PER_CU = 3;
 constexpr int CG_ENT = CLUSTER_MAX * BLOCKS_MAX;
 
 __device__ __forceinline__ int cg_find(const int32_t* a, int n, int key) {
@@ -324,7 +324,7 @@ static hipError_t launch_cocg_nz(const CocgArgs& a, hipStream_t s) {
 
 hipError_t launch_cocg(const CocgArgs& a, hipStream_t s) {
   if (a.ncols <= 0 || a.nz <= 0) return hipSuccess;
-  if (a.nz == 1 || a.ncols * a.nz <= CG_SPLIT_WG) return launch_cocg_nz<1>(a, s);
+  if (a.nz == 1 || a.ncols * a.nz <= (int64_t)CG_SPLIT_PER_CU * a.cus) return launch_cocg_nz<1>(a, s);
   return a.nz == 2 ? launch_cocg_nz<2>(a, s) : launch_cocg_nz<4>(a, s);
 }
 

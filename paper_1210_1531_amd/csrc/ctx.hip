@@ -586,6 +586,7 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
     ea.fb_list = ctx->k_fbl.as<int32_t>();
     ea.fb_count = ctx->k_fbc.as<int32_t>();
     ea.rec_cap = rec_cap;
+    ea.cus = ncu;
     ea.sweep_cap = job.eig_sweeps > 0 ? std::min(job.eig_sweeps, sweep_cap) : sweep_cap;
     ea.cvec = adj_out ? ctx->adj_cvec.as<double>() : nullptr;
     ea.cdg = adj_out ? ctx->adj_cdg.as<double>() : nullptr;
@@ -1883,6 +1884,7 @@ int mag_cocg_columns(mag_ctx* ctx, const int32_t* cols, int64_t n, const double*
   CocgArgs ca{};
   ca.cols = dcols.as<int32_t>();
   ca.ncols = n;
+  ca.cus = device_count_cus(ctx->device);
   ca.clus_ptr = ctx->clus_ptr.as<int64_t>();
   ca.clus_atoms = ctx->clus_atoms.as<int32_t>();
   ca.bptr = ctx->bptr.as<int32_t>();

@@ -42,14 +42,15 @@
 namespace mag {
 
 constexpr int ETPB = 64;
-// Up to this many columns the QL runs with a wave for each column, vectors and
-// all (ql_vec_kernel), beyond it with a lane for each column and the vectors
+// Up to this many columns per CU the QL runs with a wave for each column, vectors
+// and all (ql_vec_kernel), beyond it with a lane for each column and the vectors
 // replayed.  A wave executes only its own column's rotations, but 64 lanes all
-// the same: with few columns its shorter chain counts (64 columns, nu = 30: QL
-// and vectors 0.17 instead of 0.50 ms), with many the instructions (15,568
-// columns: 2.0 against 1.2 ms).  The two meet at 4,096 columns at every nu
-// from 12 to 48; the bits are the same.
-constexpr int64_t QL_WAVE_COLS = 4096;
+// the same: with few columns its shorter chain counts, with many the
+// instructions (column spectra of clusters with r = 3, nu = 30, 256 CUs: 512
+// columns 0.57 against 0.84 ms, 12,288 columns 4.71 against 3.96).  The two meet
+// at 5,100 columns at nu = 12, 4,200 at 20, 3,700 at 30, 4,000 at 40 and 4,150 at
+// 48, about 16 a CU; the bits are the same.
+constexpr int QL_WAVE_PER_CU = 16;
 constexpr int VEC_AHEAD = 4;  // sweeps whose records are in flight
 constexpr int QL_MAXIT = 60;  // QL iterations per eigenvalue before giving up
 
@@ -697,7 +698,7 @@ static hipError_t launch_eig_nm(const EigArgs& a, hipStream_t s) {
   const size_t lds1 = (size_t)NM * (NM + 1) * sizeof(double);
   const size_t lds3 = (size_t)NM * (NM + 1) * sizeof(double) + NM * sizeof(double) + NM * sizeof(int);
   hipLaunchKernelGGL(tri_kernel<NM>, dim3(nb), dim3(ETPB), lds1, s, a);
-  if (a.ncols <= QL_WAVE_COLS && a.sweep_cap >= eig_sweep_cap(NM)) {
+  if (a.ncols <= (int64_t)QL_WAVE_PER_CU * a.cus && a.sweep_cap >= eig_sweep_cap(NM)) {
     hipLaunchKernelGGL(ql_vec_kernel<NM>, dim3(nb), dim3(ETPB), lds3, s, a);
     return hipGetLastError();
   }

@@ -169,6 +169,7 @@ struct EigArgs {
   // solver's own order
   double* cvec;
   double* cdg;
+  int cus;                    // CUs of the device
 };
 
 struct DensityArgs {
@@ -322,6 +323,7 @@ struct CocgArgs {
   double* G;           // complex out, G[2 (off[i] nz + q len_i + c)]
   int32_t* iters;      // per column and energy: steps, or -1
   int32_t* err;
+  int cus;             // CUs of the device
 };
 hipError_t launch_cocg(const CocgArgs& a, hipStream_t s);
 // MD step helpers (md.hip)
