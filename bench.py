@@ -205,9 +205,7 @@ def launch_plans(st):
         out.append({"bucket": b, "threads": tpb, "rows_per_thread": st["plan_rows"][b],
                     "workgroups_per_cu": st["plan_per_cu"][b],
                     "cached_blocks_at_most": st["plan_cache"][b],
-                    "candidates": st["plan_candidates"][b],
-                    "columns": int(st["plan_columns"][b]),
-                    "tuned_us_per_column": st["plan_us_per_col"][b]})
+                    "columns": int(st["plan_columns"][b])})
     return out
 
 
@@ -262,9 +260,7 @@ def extra_workload(key, nu, Context, model, torch, steps, plain_sample, recomput
     t_gen = time.perf_counter()
     ctx, pos, sk, setup = build_context(Context, model, s, torch)
     opts = dict(nu=s.nu, kT=s.kT, n_electrons=s.n_electrons)
-    st0 = ctx.stats()
-    ctx.solve(**opts)  # first use: launch plans timed here
-    st_tune = ctx.stats()
+    ctx.solve(**opts)
     ctx.backward(1.0)
     ctx.forces(sk)
     torch.cuda.synchronize()
@@ -294,7 +290,6 @@ def extra_workload(key, nu, Context, model, torch, steps, plain_sample, recomput
         "fwdbwd_columns_per_s": M / (ms_fb * 1e-3), "fwdbwd_ms": ms_fb,
         "workflow_used": {0: "recompute", 1: "store"}[st["workflow_used"]],
         "krylov_buckets": st["krylov_buckets"], "krylov_threads": st["krylov_tpb"],
-        "autotune_ms": st_tune["autotune_ms"] - st0["autotune_ms"],
         "krylov_plans": launch_plans(st),
         "stage_ms": {"krylov": st["t_krylov_ms"], "eig": st["t_eig_ms"],
                      "mu_energy": st["t_mu_ms"], "pass2": st["t_pass2_ms"],
@@ -492,7 +487,6 @@ def main(argv=None):
             "workflow_used": {0: "recompute", 1: "store"}[st["workflow_used"]],
             "krylov_buckets": st["krylov_buckets"],
             "krylov_threads": st["krylov_tpb"],
-            "autotune_ms": st["autotune_ms"],
             "step": "fwd (pass 1 + mu + energy) + bwd (pass 2 rho/pi + forces through rho)",
         },
         "krylov_plans": launch_plans(st),

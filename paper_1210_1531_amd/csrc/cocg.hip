@@ -74,7 +74,7 @@ __device__ __forceinline__ void block_sums(double* v, double (*s_red)[NR]) {
   for (int k = 0; k < K; ++k) v[k] = s_red[0][k];
   // waves in a fixed order, K values at a time (a full unroll of many values
   // would hold all K x waves partial sums in registers at once)
-#pragma unroll (K <= 3 ? CG_WAVES : 1)
+#pragma unroll K <= 3 ? CG_WAVES : 1
   for (int w = 1; w < CG_WAVES; ++w) {
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] += s_red[w][k];

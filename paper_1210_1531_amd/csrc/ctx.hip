@@ -640,7 +640,7 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
       const int64_t* dqbeg = ctx->k_qbeg.as<int64_t>();
       int32_t* dqueue = ctx->k_queue.as<int32_t>();
       std::vector<const KrylovPlan*> plans(nbk, nullptr);
-      if (gl) {  // captured solve: lists are resident, plans already tuned
+      if (gl) {  // captured solve: lists are resident
         const size_t c = (size_t)(i0 / bsz);
         boff = gl->boff[c];
         dslots = gl->slots + gl->slot_base[c];
@@ -663,8 +663,6 @@ int run_columns(mag_ctx* ctx, ColumnJob& job, const GraphLists* gl = nullptr) {
           TRY(sync(ctx));  // the host lists may change or go out of scope
           if (one_chunk_order) {
             if (!same_order) ol.bucket = bucket;  // else ol.bucket is what bkt points to
-            ol.hslots = hslots;
-            ol.hqbeg = hqbeg;
             ol.boff = boff;
             ol.sys_gen = ctx->sys_gen;
             ol.cap = cap;
@@ -1500,7 +1498,7 @@ static bool graph_usable(const mag_ctx* ctx, const mag_opts& resolved) {
          same_opts(g.key, resolved);
 }
 
-// Capture the forward solve just run eagerly (all buffers sized, plans tuned):
+// Capture the forward solve just run eagerly (all buffers sized, plans made):
 // pass 1 over every chunk, the bisection and the energies, and the copy of
 // the final state to pinned host memory.  Host-side column lists of the
 // persistent launches are uploaded beforehand into buffers the graph owns.

@@ -153,10 +153,6 @@ template <int N>
 __device__ __forceinline__ double row_bcast(double x) {
   return dpp_f64<0x150 + N>(x);
 }
-template <int T>
-__device__ __forceinline__ double row_bcast_at(double x) {
-  return row_bcast<T>(x);
-}
 
 __device__ __forceinline__ double lane_value(double v, int src) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
@@ -278,7 +274,6 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
   static_assert(pool_bytes(ROWS, NCOL, NSET) + LDS_STATIC <= LDS_CU, "LDS of a CU");
   __shared__ int32_t s_atoms[CLUSTER_MAX];
   __shared__ int32_t s_brow[CLUSTER_MAX];   // first global block of each cluster atom's row
-  __shared__ int32_t s_rowb[CLUSTER_MAX];   // the same by rank
   __shared__ __attribute__((aligned(16))) uint16_t s_key[CLUSTER_MAX];
   __shared__ uint8_t s_pos[CLUSTER_MAX];    // rank of each cluster atom
   __shared__ uint8_t s_orig[CLUSTER_MAX];   // cluster atom of each rank
@@ -310,7 +305,6 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
   const int wv = NCOL == 2 ? wave % WPC : wave;
   const int g = (lane >> 4) & 1;
   const int p0 = wv * 32 + (lane >> 5) * 16 + (lane & 15);
-  const bool bit1 = (lane & 2) != 0;
   int tabJ = -1;  // atom whose cluster tables the LDS holds (-1: none)
   const char* bval = reinterpret_cast<const char*>(a.bval);
 
@@ -407,7 +401,6 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
         if (tid < CLUSTER_MAX) {
           s_key[tid] = 0;
           s_patb[tid] = -1;
-          s_rowb[tid] = 0;
           s_len[tid] = 0;
           s_blen[tid] = 0;
         }
@@ -487,7 +480,6 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
             s_pos[i] = (uint8_t)r;
             s_orig[r] = (uint8_t)i;
             s_len[r] = (uint8_t)(key >> 8);
-            s_rowb[r] = s_brow[i];
           }
         }
         __syncthreads();

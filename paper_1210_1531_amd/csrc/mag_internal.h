@@ -213,7 +213,6 @@ hipError_t launch_mu_round(const double* eps, const double* w, const int32_t* nu
                            int nu, MuState* st, double* partials, int grid, hipStream_t s);
 hipError_t launch_energy(const double* eps, const double* w, const int32_t* nu_eff, int64_t M,
                          int nu, MuState* st, double* partials, int grid, hipStream_t s);
-int mu_points_per_round();
 int mu_levels_per_round();
 
 // clusters
@@ -454,7 +453,6 @@ struct mag_ctx {
     int cap = 0;
     uint64_t slots_epoch = 0, qbeg_epoch = 0;
     std::vector<int8_t> bucket;
-    std::vector<int32_t> hslots;
-    std::vector<int64_t> hqbeg, boff;
+    std::vector<int64_t> boff;
   } lists;
 };

@@ -28,7 +28,6 @@ constexpr int MTPB = 256;
 constexpr int MLEV = 5;
 constexpr int MPTS = (1 << MLEV) - 1;  // 31
 
-int mu_points_per_round() { return MPTS; }
 int mu_levels_per_round() { return MLEV; }
 
 __device__ __forceinline__ double fermi_mu(double x) {

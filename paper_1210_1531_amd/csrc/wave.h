@@ -103,21 +103,6 @@ __device__ __forceinline__ double rs_half_mirror(double a, double b) {
   return keep + recv;
 }
 
-// 16 values per lane -> the return value is the wave total of value
-// 8 b5 + 4 b4 + 2 b2 + b3 (b_n: bit n of the lane id), the same in each quad
-__device__ __forceinline__ double reduce16(double* v) {
-#pragma unroll
-  for (int t = 0; t < 8; ++t) v[t] = swap32_add(v[t], v[t + 8]);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) v[t] = swap16_add(v[t], v[t + 4]);
-  const double u0 = rs_mirror(v[0], v[1]);
-  const double u1 = rs_mirror(v[2], v[3]);
-  double r = rs_half_mirror(u0, u1);
-  r += dpp_f64<DPP_QUAD_XOR2>(r);
-  r += dpp_f64<DPP_QUAD_XOR1>(r);
-  return r;
-}
-
 // 8 values per lane -> the wave total of value 4 b5 + 2 b4 + b3, the same in
 // each group of eight lanes
 __device__ __forceinline__ double reduce8(double* v) {
