@@ -404,7 +404,8 @@ __global__ __launch_bounds__(KTPB) void adjoint_kernel(AdjointArgs a) {
     for (int alpha = al0; alpha < (SPLIT ? al0 + 1 : NORB); ++alpha) {
       const int64_t slot = 4 * ia + alpha;
       // ---- the forward pass's Krylov data of this column: its basis (in
-      // registers, as the forward holds it), h, beta and the last residual
+      // registers, all of its vectors at a thread's row), h, beta and the last
+      // residual
       const int n = a.nu_eff[slot];
       if (n < 1 || n > NU) continue;  // a failed column (the forward flagged it)
       double qv[R][NU];

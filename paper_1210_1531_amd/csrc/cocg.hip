@@ -15,9 +15,10 @@
 // an iteration is the reads of those blocks, 16 bytes per lane at a time
 // through the texture unit, so with one energy a row's first blocks are kept
 // in registers and each other one is read while the one before is used.  The
-// arithmetic of an energy is the same in all of them, bit for bit.  Reductions are per-wave all-reduces plus a
-// fixed-order cross-wave sum, so every thread sees the same sums and the
-// per-energy control flow is uniform across the workgroup.
+// arithmetic of an energy is the same in all of them, bit for bit.  Reductions
+// are per-wave all-reduces plus a fixed-order cross-wave sum, so every thread
+// sees the same sums and the per-energy control flow is uniform across the
+// workgroup.
 #include <algorithm>
 
 #include "mag_internal.h"
@@ -28,7 +29,8 @@ namespace mag {
 constexpr int CG_TPB = NC_MAX;  // one thread per cluster orbital
 constexpr int CG_WAVES = CG_TPB / 64;
 // The blocks of a row that stay in registers over all iterations (one energy per
-// workgroup): as many as fit 168 registers, three waves on a SIMD
+// workgroup): as many as fit 168 registers, three waves on a SIMD (all but one
+// register: it spills)
 constexpr int CG_KEPT = 3;
 // Up to this many (column, energy) pairs per CU a workgroup takes one energy: the
 // chip has room for them all, and an iteration is shorter (64 columns of 4

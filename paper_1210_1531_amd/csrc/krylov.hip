@@ -33,9 +33,12 @@
 // Reductions run in a fixed order that depends on the cluster and on nu only,
 // so a column's bits depend neither on the launch nor on its partner column.
 //
-// What bounds it: the instruction issue of a step's serial chain (SpMV, local
-// subtraction, dots, subtraction, three barriers between them), with two waves
-// on each SIMD, as many as the basis registers leave room for.  A step of two
+// What bounds it: latency along a step's serial chain (SpMV, local subtraction,
+// dots, subtraction, three barriers between them), with two waves on each SIMD,
+// as many as the basis registers leave room for: a wave waits for memory or a
+// barrier in 45% of its cycles, for an issue slot in 21%, and issues in 34%; a
+// SIMD's vector pipe is active 42% of the time, its matrix pipe 15% (nu = 30, all
+// 15,568 columns of 3,892 atoms).  A step of two
 // columns in clusters of about 156 atoms takes about 14,000 cycles: SpMV 5,600
 // (a third of it from the cache), local subtraction 1,500, dots 1,300, totals,
 // subtraction and store 4,100; the projection adds about 5,000 per step.
@@ -781,7 +784,7 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
         store_q(w, k + 1, go, own_x, s_x + ((k & 1) ^ 1) * XB);
       };
       // a condition that all lanes share, as a scalar up to nu = 30; beyond that it
-      // stays in the lanes (forces of 3,600 atoms at nu = 40: 16.4 against 16.9 ms)
+      // stays in the lanes (forces of 3,600 atoms at nu = 40: 16.0 against 16.3 ms)
       auto any = [](bool c) { return NU > 30 ? c : __builtin_amdgcn_ballot_w64(c) != 0; };
       bool more = true;
       for (int k = 0; k < nu_max && more; ++k) {
@@ -1129,8 +1132,8 @@ __global__ __launch_bounds__(KTPB) void krylov_kernel(KrylovArgs a) {
 // Two columns take 200 registers at nu = 40 and 160 atoms, 192 at nu = 48 and 128:
 // some of the rest then lives in scratch, which still costs less than a
 // workgroup for one column (3,892 atoms, r = 6, nu = 40: 15.9 against 17.3 ms).
-// Beyond that a cluster takes the whole workgroup for one column.  A column's shape follows from nu and its
-// cluster's size alone: a smaller shape has fewer instructions per step and
+// Beyond that a cluster takes the whole workgroup for one column.  A column's
+// shape follows from nu and its cluster's size alone: a smaller shape has fewer instructions per step and
 // holds more of H in LDS, so the smallest that holds a cluster is the fastest
 // one (160-atom clusters at nu = 30: 7.3 ms with 5 rows against 9.9 ms with 6).
 struct ShapeDef {
